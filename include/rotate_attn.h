@@ -220,7 +220,7 @@ int rotate_attn_quantize_qkv(const ra_params* p, const void* q, const void* k, c
  * (the affine code P~ = u - 8, Sec. 4.2.1), PV on the codes,
  * O = (sum of dequantized PV) / l + mu_v, l = sum of the unquantized P.  The
  * container selects the matrix-core path: RA_CODES_E2M3 runs the FP6 matrix
- * core (v_mfma_scale_f32_*_f8f6f4, codes as E2M3 values, binary32 sums that are
+ * core (v_mfma_f32_*_f8f6f4, codes as E2M3 values, binary32 sums that are
  * exact for these integers); RA_CODES_INT4 runs the int8 matrix core
  * (v_mfma_i32_32x32x32_i8 on the unpacked nibbles, int32 accumulation).  Both
  * compute the same integers.

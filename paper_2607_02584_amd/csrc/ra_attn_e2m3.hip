@@ -9,7 +9,7 @@
 // core stay integer multiples of 1/8 far below 2^24, so
 //   S  = Q~ K~^T                         is the exact integer score, and
 //   O' += (u/8) V~                       is exact per block,
-// on v_mfma_scale_f32_32x32x64_f8f6f4, which runs at twice the int8 rate and
+// on v_mfma_f32_32x32x64_f8f6f4, which runs at twice the int8 rate and
 // accumulates in binary32: PV accumulates straight into the output tile.
 //
 // Per block of KV keys (ascending):
@@ -75,10 +75,16 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBlockM = 32 * kWaves;  // queries per workgroup
-constexpr int kScaleOne = 127;  // E8M0 block scale 2^0
 
+// The form without block scales: with both scale operands the constant 0 the
+// compiler issues v_mfma_f32_32x32x64_f8f6f4, whose scale is 1, instead of the
+// scaled instruction with scales of 2^0.  The results are the same bits; the
+// scaled form is a pair of instruction words whose first half takes an issue
+// slot of its own, and the vector unit binds this kernel (8 exponentials and a
+// product: 84 cycles scaled, 76 without, four waves per SIMD; the
+// 32760-token, 12-head layer: 2.93 -> 2.87 ms).
 __device__ __forceinline__ v16f mfma6(v8i a, v8i b, v16f c) {
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, kScaleOne, 0, kScaleOne);
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 0, 0, 0);
 }
 
 // 32 binary32 values -> 32 E2M3 codes (value / 8, round to nearest even), the
