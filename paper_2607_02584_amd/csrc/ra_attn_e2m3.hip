@@ -197,6 +197,78 @@ struct TilePiece {
   }
 };
 
+// The end of a wave's 32 query rows from q0 on: O = O' * 8 w / 15 / l + mu_v,
+// rotated back by H when V was rotated online, in the output type.  Lane
+// (j, hh) holds channel 32 mt + j of the queries 8 (r / 4) + 4 hh + r % 4; l is
+// the lane's part of pscale * sum of P (LQ: of the sum of the codes u), w the
+// final V scale per channel.
+template <typename T, typename F>
+__device__ __forceinline__ void store_rows(T* o, const v16f (&of)[4], int N, int q0, int hh, F conv) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int qi = 8 * (r >> 2) + 4 * hh + (r & 3);
+    if (q0 + qi < N) {
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) o[qi * kD + mt * 32] = conv(of[mt][r]);
+    }
+  }
+}
+
+__device__ __forceinline__ void finish_rows(const AttnArgs& a, v16f (&of)[4], float l, const float* w, int bh, int q0,
+                                            int hh, int j) {
+  const float ltot = l + __shfl_xor(l, 32);
+  const float k2 = 8.0f;
+  const float* muv = a.mu_v ? a.mu_v + bh * kD : nullptr;
+  float wsc[4], mu[4];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    wsc[mt] = w[mt * 32 + j] * k2;
+    mu[mt] = muv ? muv[mt * 32 + j] : 0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int qi = 8 * (r >> 2) + 4 * hh + (r & 3);
+    const float inv = 1.0f / __shfl(ltot, qi);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) of[mt][r] = of[mt][r] * wsc[mt] * inv + mu[mt];
+  }
+  if (a.vhad) {
+    // V came rotated by H: each query row goes back, O = O' H^T = O' H.  Channel
+    // 32 mt + j: strides 64 and 32 pair tiles mt ^ 2 and mt ^ 1 in the thread,
+    // strides 16 .. 1 pair lanes j ^ 16 .. j ^ 1 (the lane with the bit set
+    // takes the difference); then the factor 1/sqrt(128).
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float t0 = of[0][r] + of[2][r], t2 = of[0][r] - of[2][r];
+      const float t1 = of[1][r] + of[3][r], t3 = of[1][r] - of[3][r];
+      of[0][r] = t0 + t1;
+      of[1][r] = t0 - t1;
+      of[2][r] = t2 + t3;
+      of[3][r] = t2 - t3;
+#pragma unroll
+      for (int msk = 16; msk >= 1; msk >>= 1) {
+        const bool upper = (j & msk) != 0;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+          const float o = __shfl_xor(of[mt][r], msk);
+          of[mt][r] = upper ? o - of[mt][r] : of[mt][r] + o;
+        }
+      }
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) of[mt][r] *= kInvSqrtD;
+    }
+  }
+  // one loop per output type: the choice is made once, not per element
+  const size_t ob = (static_cast<size_t>(bh) * a.N + q0) * kD + j;
+  if (a.out_dtype == 2)
+    store_rows(static_cast<float*>(a.o) + ob, of, a.N, q0, hh, [](float v) { return v; });
+  else if (a.out_dtype == 0)
+    store_rows(static_cast<uint16_t*>(a.o) + ob, of, a.N, q0, hh,
+               [](float v) { return __bfloat16_as_ushort(__float2bfloat16(v)); });
+  else
+    store_rows(static_cast<uint16_t*>(a.o) + ob, of, a.N, q0, hh, [](float v) { return __half_as_ushort(__float2half(v)); });
+}
+
 // QB: Q smoothing, every key carries the score bias fl(b_j Kc), the scores
 // become t = fma(S, c, bias) before the maximum and P = 2^(t - m).
 // LQ: the normaliser sums the codes u = rint(pscale P) (l = sum of P^) instead of pscale P.
@@ -216,8 +288,11 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
   // the wave index is uniform: conditions on it are scalar branches
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hh = lane >> 5, j = lane & 31;
-  int bh, qtile;
-  xcd_tile(bh, qtile);
+  // the launch covers the first gridDim.x of the list of 256-query tiles (head
+  // by head); the split kernel covers the others
+  const int ntile = (a.Npad + kBlockM - 1) / kBlockM;
+  const int L = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+  const int bh = L / ntile, qtile = L - bh * ntile;
   const int qrow = qtile * kBlockM + wave * 32 + j;
   const int N = a.N;
   const int nblocks = (N + KV - 1) / KV;
@@ -311,15 +386,20 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
   // already in LDS while block j is processed (its score products run during
   // block j's probabilities), and block j + 2's are written during block j.
   const int t1 = nblocks > 1 ? 1 : 0, t2 = nblocks > 2 ? 2 : nblocks - 1;
+  // All requests of the prologue go out before the first is waited for.
   TilePiece<KV> tp;
-  tp.load(kbase, vbase, tid);
-  tp.store(sK[0], sV[0], tid);
-  tp.load(kbase + t1 * KB, vbase + t1 * KB, tid);
-  tp.store(sK[1], sV[1], tid);
-  tp.load(kbase + t2 * KB, vbase + t2 * KB, tid);
-  store_aux(0, 0, fetch_aux(0));
   Aux pf{0.f, 0.f, 0.f};
-  if (nblocks > 1) pf = fetch_aux(1);
+  {
+    TilePiece<KV> tp0;
+    tp0.load(kbase, vbase, tid);
+    tp.load(kbase + t1 * KB, vbase + t1 * KB, tid);
+    const Aux f0 = fetch_aux(0);
+    if (nblocks > 1) pf = fetch_aux(1);
+    tp0.store(sK[0], sV[0], tid);
+    tp.store(sK[1], sV[1], tid);
+    store_aux(0, 0, f0);
+  }
+  tp.load(kbase + t2 * KB, vbase + t2 * KB, tid);
   __syncthreads();
 
   // ---- S^T = K Q^T (exact integer scores in binary32), chunks c0 and c0 + 1
@@ -460,7 +540,10 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
         cch[ch] = __fmul_rn(cq, sKc[buf][ch]);
-        tmax = fmaxf(tmax, __fmul_rn(chunk_max(s[ch]), cch[ch]));
+        const float mx = chunk_max(s[ch]);
+        // a wholly masked chunk has no maximum, whatever its scale (0 when its
+        // scale group holds no token: the product would be a zero score)
+        if (!MASKED || mx > -3.0e38f) tmax = fmaxf(tmax, __fmul_rn(mx, cch[ch]));
       }
     } else {
 #pragma unroll
@@ -628,71 +711,412 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
   if (tid < kD) sW[tid] = wcur;
   __syncthreads();
 
-  // ---- epilogue: O = O' * 8 w / 15 / l + mu_v; lane (j, hh) holds channel
-  //      32 mt + j of the wave's queries 8 (r / 4) + 4 hh + r % 4 ----
-  const float ltot = l + __shfl_xor(l, 32);   // pscale * sum of P (LQ: sum of the codes u)
-  const float k2 = 8.0f;
-  const float* muv = a.mu_v ? a.mu_v + bh * kD : nullptr;
-  float wsc[4], mu[4];
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    wsc[mt] = sW[mt * 32 + j] * k2;
-    mu[mt] = muv ? muv[mt * 32 + j] : 0.f;
+  finish_rows(a, of, l, sW, bh, qtile * kBlockM + wave * 32, hh, j);
+}
+
+// ------------------------------------------------ key-split variant (KV = 128) --
+// The same rows by workgroups of 4 waves and 64 queries: wave (qs, kh) takes
+// query rows 32 qs .. 32 qs + 31 and the 64-key group kh of every 128-key
+// block, so a block's chain of vector work is half as long and a 256-query
+// tile becomes four workgroups.  The two waves of a query row share its
+// running maximum: each computes the maximum over its own group once the
+// group's scores are known, at the end of the block before, and leaves it in
+// LDS across the block barrier (no barrier more than the plain kernel has).
+// Each keeps its own row sums and its own O' over its keys, added at the end.
+// The V-ratio multiplies of O' are done twice (once per key half), which is
+// why the plain kernel stays the better one wherever it fills the chip.
+constexpr int kSplitThreads = 256;
+constexpr int kSplitM = 64;   // queries per workgroup
+
+struct SplitPiece {
+  // three 16-byte pieces of K and of V per thread cover a 128-key tile
+  typedef unsigned T __attribute__((ext_vector_type(4)));
+  T k0, k1, k2, v0, v1, v2;
+  __device__ __forceinline__ void load(const uint8_t* kg, const uint8_t* vg, int tid) {
+    const T* K = reinterpret_cast<const T*>(kg) + tid;
+    const T* V = reinterpret_cast<const T*>(vg) + tid;
+    k0 = K[0];
+    v0 = V[0];
+    k1 = K[kSplitThreads];
+    v1 = V[kSplitThreads];
+    k2 = K[2 * kSplitThreads];
+    v2 = V[2 * kSplitThreads];
   }
-  const int q0 = qtile * kBlockM + wave * 32;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int qi = 8 * (r >> 2) + 4 * hh + (r & 3);
-    const float inv = 1.0f / __shfl(ltot, qi);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) of[mt][r] = of[mt][r] * wsc[mt] * inv + mu[mt];
+  __device__ __forceinline__ void store(uint8_t* ks, uint8_t* vs, int tid) const {
+    T* K = reinterpret_cast<T*>(ks) + tid;
+    T* V = reinterpret_cast<T*>(vs) + tid;
+    K[0] = k0;
+    V[0] = v0;
+    K[kSplitThreads] = k1;
+    V[kSplitThreads] = v1;
+    K[2 * kSplitThreads] = k2;
+    V[2 * kSplitThreads] = v2;
   }
-  if (a.vhad) {
-    // V came rotated by H: each query row goes back, O = O' H^T = O' H.  Channel
-    // 32 mt + j: strides 64 and 32 pair tiles mt ^ 2 and mt ^ 1 in the thread,
-    // strides 16 .. 1 pair lanes j ^ 16 .. j ^ 1 (the lane with the bit set
-    // takes the difference); then the factor 1/sqrt(128).
+};
+
+// tile0: the first 256-query tile of the list this launch covers.
+template <bool KTOK, bool SYM7, bool DEBUG, bool QB, bool LQ>
+__global__ __launch_bounds__(kSplitThreads, DEBUG ? 1 : 2) void k_attn_e2m3_split(AttnArgs a, int tile0) {
+  constexpr int KV = 128;
+  constexpr int KB = KV * 96;
+  static_assert(KB == 3 * kSplitThreads * 16, "three pieces per thread");
+  // K tiles of blocks j, j + 1, j + 2 (block index mod 3), then their V tiles;
+  // at the end the upper key halves' O'
+  __shared__ __align__(16) uint8_t sT[6 * KB];
+  // side data of block j in slot j % 4: it is staged two blocks ahead, because
+  // the maximum of block j + 1 is taken in block j
+  __shared__ __align__(16) float sR[4][kD];
+  __shared__ __align__(16) float sW[kD];
+  __shared__ __align__(16) float sKs[4][KTOK ? KV : 1];
+  __shared__ __align__(16) float sKc[4][4];
+  __shared__ __align__(16) float sB[4][QB ? KV : 1];
+  __shared__ float sM[2][4][32];   // group maxima of block j, slot j % 2, per wave
+  __shared__ float sL[2][64];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hh = lane >> 5, j = lane & 31;
+  const int qs = wave & 1, kh = wave >> 1;
+  const int ntile = (a.Npad + kBlockM - 1) / kBlockM;
+  const int U = 4 * tile0 + xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+  const int bh = (U >> 2) / ntile;
+  const int wq0 = ((U >> 2) - bh * ntile) * kBlockM + (U & 3) * kSplitM;
+  if (wq0 >= a.N) return;   // the last tile of a head may reach past its tokens
+  const int q0 = wq0 + qs * 32, qrow = q0 + j;
+  const int N = a.N;
+  const int nblocks = (N + KV - 1) / KV;
+  const int kstride = a.Npad / a.k_group;
+  constexpr float kLog2P = SYM7 ? 2.80735492205760410f : 3.90689059560851852f;
+  const size_t hcode = static_cast<size_t>(bh) * a.Npad * 96;
+  const uint8_t* kbase = a.kc + hcode;
+  const uint8_t* vbase = a.vc + hcode;
+  const float* ksh = a.ks + static_cast<size_t>(bh) * kstride;
+  auto ktile = [&](int t) { return sT + t * KB; };
+  auto vtile = [&](int t) { return sT + (3 + t) * KB; };
+
+  // (rows below N, hence below Npad, exist in full 128-row tiles)
+  v8i qop[2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float t0 = of[0][r] + of[2][r], t2 = of[0][r] - of[2][r];
-      const float t1 = of[1][r] + of[3][r], t3 = of[1][r] - of[3][r];
-      of[0][r] = t0 + t1;
-      of[1][r] = t0 - t1;
-      of[2][r] = t2 + t3;
-      of[3][r] = t2 - t3;
+  for (int kc = 0; kc < 2; ++kc) {
+    const int rec = (((qrow >> 5) * 2 + kc) * 2 + hh) * 32 + (qrow & 31);
+    qop[kc] = load_rec(a.qc + hcode + static_cast<size_t>(rec) * 24);
+  }
+  const float cq = __fmul_rn(a.qs[static_cast<size_t>(bh) * (a.Npad / a.q_group) + qrow / a.q_group], a.Kc);
+
+  // side data, as in the plain kernel: waves 0 and 1 the V scales (thread =
+  // channel), waves 2 and 3 key tid - 128, or wave 2 the scale of chunk t
+  struct Aux {
+    float v, k, b;
+  };
+  int fg = 0, fr = 0;
+  const int kgs = __builtin_ctz(static_cast<unsigned>(a.k_group));
+  auto fetch_aux = [&](int jb) {
+    Aux f{0.f, 0.f, 0.f};
+    if (wave < 2) f.v = a.vs[(static_cast<size_t>(bh) * a.nvgroups + fg) * kD + tid];
+    if (++fr == a.v_bpg) {
+      fr = 0;
+      ++fg;
+    }
+    const int kt = tid - kD;
+    if (KTOK) {
+      if (wave >= 2) f.k = ksh[(jb * KV + kt) >> kgs];
+    } else if (wave == 2 && lane < 4) {
+      f.k = ksh[(jb * KV + kt * 32) >> kgs];
+    }
+    if (QB && wave >= 2) f.b = a.kbias[static_cast<size_t>(bh) * a.Npad + jb * KV + kt];
+    return f;
+  };
+  float wcur = 1.0f;
+  auto store_aux = [&](int jb, const Aux& f) {
+    const int buf = jb & 3;
+    if (wave < 2) {
+      float r = 1.0f;
+      if (f.v > 0.0f) {
+        r = (jb == 0) ? 1.0f : wcur * __builtin_amdgcn_rcpf(f.v);
+        wcur = f.v;
+      }
+      sR[buf][(tid & 31) * 4 + (tid >> 5)] = r;
+    }
+    const int kt = tid - kD;
+    if (KTOK) {
+      if (wave >= 2) sKs[buf][kt] = f.k;
+    } else if (wave == 2 && lane < 4) {
+      sKc[buf][kt] = f.k;
+    }
+    if (QB && wave >= 2) sB[buf][kt] = __fmul_rn(f.b, a.Kc);
+  };
+
+  v16f of[4];
 #pragma unroll
-      for (int msk = 16; msk >= 1; msk >>= 1) {
-        const bool upper = (j & msk) != 0;
+  for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-          const float o = __shfl_xor(of[mt][r], msk);
-          of[mt][r] = upper ? o - of[mt][r] : of[mt][r] + o;
+    for (int r = 0; r < 16; ++r) of[mt][r] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  int vr = 0;
+
+  const int t1 = nblocks > 1 ? 1 : 0, t2 = nblocks > 2 ? 2 : nblocks - 1;
+  SplitPiece tp;
+  Aux pf{0.f, 0.f, 0.f};
+  {
+    SplitPiece tp0;
+    tp0.load(kbase, vbase, tid);
+    tp.load(kbase + t1 * KB, vbase + t1 * KB, tid);
+    const Aux f0 = fetch_aux(0);
+    Aux f1{0.f, 0.f, 0.f};
+    if (nblocks > 1) f1 = fetch_aux(1);
+    if (nblocks > 2) pf = fetch_aux(2);
+    tp0.store(ktile(0), vtile(0), tid);
+    tp.store(ktile(1), vtile(1), tid);
+    store_aux(0, f0);
+    if (nblocks > 1) store_aux(1, f1);
+  }
+  tp.load(kbase + t2 * KB, vbase + t2 * KB, tid);
+  __syncthreads();
+
+  v16f s[2];   // scores of the wave's two chunks, 2 kh and 2 kh + 1
+  v8i kr[4];
+  auto read_kpair = [&](const uint8_t* kt) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      kr[t] = load_rec(&kt[((((2 * kh + (t & 1)) * 2 + (t >> 1)) * 2 + hh) * 32 + j) * 24]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto score_pair = [&]() {
+    v16f z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    s[0] = mfma6(kr[0], qop[0], z);
+    s[1] = mfma6(kr[1], qop[0], z);
+    s[0] = mfma6(kr[2], qop[1], s[0]);
+    s[1] = mfma6(kr[3], qop[1], s[1]);
+  };
+  const bool dbg = DEBUG && bh == a.dbg_bh && qrow >= a.dbg_row0 && qrow < a.dbg_row0 + a.dbg_rows;
+  const size_t dbg_off = static_cast<size_t>(qrow - a.dbg_row0) * N;
+  // key of register r of the wave's chunk c within its block
+  auto klocal = [&](int c, int r) { return (2 * kh + c) * 32 + 8 * (r >> 2) + 4 * hh + (r & 3); };
+  // The scores of block jn are in s: mask keys past N (last block), take the
+  // group's maximum of fl(S c) (or of t = fma(S, c, bias), which replaces S)
+  // and leave it for the row's other wave.
+  float gmax = -INFINITY;
+  auto finish_scores = [&](int jn) {
+    const int buf = jn & 3;
+    if (DEBUG && dbg && a.dbg_s) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = jn * KV + klocal(c, r);
+          if (key < N) a.dbg_s[dbg_off + key] = static_cast<int32_t>(s[c][r]);
+        }
+    }
+    if (jn == nblocks - 1 && N % KV != 0) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (jn * KV + klocal(c, r) >= N) s[c][r] = -INFINITY;
+    }
+    gmax = -INFINITY;
+    if (QB || KTOK) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const float cc = KTOK ? 0.f : __fmul_rn(cq, sKc[buf][2 * kh + c]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float ce = KTOK ? __fmul_rn(cq, sKs[buf][klocal(c, r)]) : cc;
+          float t;
+          if (QB) {
+            t = __fmaf_rn(s[c][r], ce, sB[buf][klocal(c, r)]);
+            if (s[c][r] == -INFINITY) t = -INFINITY;
+            s[c][r] = t;
+          } else {
+            t = __fmul_rn(s[c][r], ce);   // NaN (ignored by the maximum) for a masked key with scale 0
+          }
+          gmax = fmaxf(gmax, t);
+          // read no further ahead than four keys (both kinds) or a chunk: registers
+          if (r == 15 || (QB && KTOK && (r & 3) == 3)) __builtin_amdgcn_sched_barrier(0);
         }
       }
+    } else {
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) of[mt][r] *= kInvSqrtD;
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int qi = 8 * (r >> 2) + 4 * hh + (r & 3);
-    if (q0 + qi < N) {
-      const size_t obase = (static_cast<size_t>(bh) * N + q0 + qi) * kD + j;
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const float v = of[mt][r];
-        if (a.out_dtype == 2) static_cast<float*>(a.o)[obase + mt * 32] = v;
-        else if (a.out_dtype == 0) static_cast<uint16_t*>(a.o)[obase + mt * 32] = __bfloat16_as_ushort(__float2bfloat16(v));
-        else static_cast<uint16_t*>(a.o)[obase + mt * 32] = __half_as_ushort(__float2half(v));
+      for (int c = 0; c < 2; ++c) {
+        // a wholly masked chunk has no maximum, whatever its scale
+        const float mx = chunk_max(s[c]);
+        const float t = __fmul_rn(mx, __fmul_rn(cq, sKc[buf][2 * kh + c]));
+        gmax = fmaxf(gmax, mx > -3.0e38f ? t : -INFINITY);
       }
     }
+    gmax = max_halves(gmax);
+    if (hh == 0) sM[jn & 1][wave][j] = gmax;
+  };
+
+  read_kpair(ktile(0));
+  score_pair();
+  finish_scores(0);
+  __syncthreads();
+  int tb = 0;
+
+  auto step = [&](int jb, auto last_tag) {
+    constexpr bool LAST = decltype(last_tag)::value;
+    const int buf = jb & 3;
+    const int tbn = tb == 2 ? 0 : tb + 1;
+    const int tbw = tbn == 2 ? 0 : tbn + 1;
+    if (!LAST && jb + 2 < nblocks) {
+      store_aux(jb + 2, pf);
+      if (jb + 3 < nblocks) pf = fetch_aux(jb + 3);
+    }
+    v8i vrec[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      vrec[t] = load_rec(&vtile(tb)[(((kh * 4 + t) * 2 + hh) * 32 + j) * 24]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bool vchange = vr == 0 && jb > 0;
+    if (++vr == a.v_bpg) vr = 0;
+    const float mnew = fmaxf(m, fmaxf(gmax, sM[jb & 1][wave ^ 2][j]));
+    const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+    m = mnew;
+    const float mq = __fsub_rn(mnew, kLog2P);
+    if (vchange) {
+      const float4 rr = *reinterpret_cast<const float4*>(&sR[buf][4 * j]);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        of[0][r] = __fmul_rn(of[0][r], rr.x);
+        of[1][r] = __fmul_rn(of[1][r], rr.y);
+        of[2][r] = __fmul_rn(of[2][r], rr.z);
+        of[3][r] = __fmul_rn(of[3][r], rr.w);
+      }
+    }
+    const unsigned long long moved = __ballot(alpha != 1.0f);
+    if (moved) {
+      const float ab = __int_as_float(
+          __builtin_amdgcn_update_dpp(__float_as_int(alpha), __float_as_int(alpha), 0x12C, 0xC, 0xF, false));
+      rescale_group<0>(of, ab, moved);
+      rescale_group<1>(of, ab, moved);
+      rescale_group<2>(of, ab, moved);
+      rescale_group<3>(of, ab, moved);
+    }
+    float ls[4];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const float cc = QB || KTOK ? 0.f : __fmul_rn(cq, sKc[buf][2 * kh + c]);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float P;   // pscale * P
+        if (QB) {
+          P = __builtin_amdgcn_exp2f(__fsub_rn(s[c][r], mq));
+        } else {
+          const float ce = KTOK ? __fmul_rn(cq, sKs[buf][klocal(c, r)]) : cc;
+          P = __builtin_amdgcn_exp2f(__fmaf_rn(s[c][r], ce, -mq));
+        }
+        if (LAST && s[c][r] == -INFINITY) P = 0.f;
+        const float lv = LQ ? __builtin_rintf(P) : P;
+        if (c == 0 && r < 4) ls[r] = lv;
+        else ls[r & 3] += lv;
+        s[c][r] = P;
+      }
+      if (KTOK) __builtin_amdgcn_sched_barrier(0);
+    }
+    const v6i pk6 = pack_fp6(s[0], s[1]);
+    const v8i B = v8i{pk6[0], pk6[1], pk6[2], pk6[3], pk6[4], pk6[5], 0, 0};
+    if (DEBUG && dbg) {
+      if (a.dbg_u) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = jb * KV + klocal(c, r);
+            const int bit = 6 * (2 * r + c);
+            uint32_t w = static_cast<uint32_t>(pk6[bit >> 5]) >> (bit & 31);
+            if ((bit & 31) > 26) w |= static_cast<uint32_t>(pk6[(bit >> 5) + 1]) << (32 - (bit & 31));
+            if (key < N) a.dbg_u[dbg_off + key] = static_cast<uint8_t>(w & 63);
+          }
+      }
+      if (a.dbg_m && hh == 0 && kh == 0) a.dbg_m[static_cast<size_t>(qrow - a.dbg_row0) * nblocks + jb] = mnew;
+    }
+    // the next block's scores first: its maximum waits for them (except where
+    // both kinds of per-key values leave no registers for K and V records at once)
+    constexpr bool PV_FIRST = KTOK && QB;
+    auto pv = [&]() {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) of[t] = mfma6(B, vrec[t], of[t]);
+    };
+    if (PV_FIRST) {
+      pv();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!LAST) {
+      read_kpair(ktile(tbn));
+      score_pair();
+    }
+    if (!PV_FIRST) pv();
+    l = __fmaf_rn(l, alpha, (ls[0] + ls[1]) + (ls[2] + ls[3]));
+    if (!LAST) {
+      // block j + 2's tiles into the buffers block j - 1 used, block j + 3's
+      // requested (after the maximum, whose registers they would take)
+      tp.store(ktile(tbw), vtile(tbw), tid);
+      __builtin_amdgcn_sched_barrier(0);
+      finish_scores(jb + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const size_t nb3 = static_cast<size_t>(jb + 3 < nblocks ? jb + 3 : nblocks - 1) * KB;
+      tp.load(kbase + nb3, vbase + nb3, tid);
+    }
+    tb = tbn;
+    __syncthreads();
+  };
+  for (int jb = 0; jb + 1 < nblocks; ++jb) step(jb, std::integral_constant<bool, false>());
+  step(nblocks - 1, std::integral_constant<bool, true>());
+
+  // the upper key half's O' and row sums join the lower half's (every tile has
+  // been read: the last step ends with a barrier)
+  if (tid < kD) sW[tid] = wcur;
+  float* ox = reinterpret_cast<float*>(sT) + qs * 64 * 64 + lane;
+  if (kh == 1) {
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ox[(mt * 16 + r) * 64] = of[mt][r];
+    sL[qs][lane] = l;
   }
+  __syncthreads();
+  if (kh == 1) return;
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) of[mt][r] += ox[(mt * 16 + r) * 64];
+  finish_rows(a, of, l + sL[qs][lane], sW, bh, q0, hh, j);
+}
+
+// Which of the 256-query tiles run on the plain kernel and which on the
+// key-split one (KV = 128).  A round is one plain workgroup on every compute
+// unit; a last round of at most half the units leaves the others idle, and its
+// tiles, split in four, run two workgroups to a unit (one wave of each per
+// SIMD) in less than a plain round: 0.69 of it at up to a quarter of the units,
+// 0.85 at half (measured, both ways, at 7800 tokens: 2 heads 150 -> 111 us, 4
+// heads 154 -> 135 us; 32760 tokens and 3 heads 1013 -> 942 us; 1024 tokens and
+// 2 heads 43 -> 37 us).  Above half the split tiles take two rounds and lose:
+// 7800 tokens and 6 heads 161 -> 224 us, 1024 tokens and 40 heads 53 -> 64 us.
+struct TilePlan {
+  int plain, split;   // tiles of the linear list: the first `plain`, then `split`
+};
+inline TilePlan plan_tiles(int total) {
+  constexpr int kUnits = 256;   // compute units of the chip
+  const int rest = total % kUnits;
+  if (2 * rest > kUnits) return {total, 0};
+  return {total - rest, rest};
 }
 
 template <int KV, bool KTOK, bool SYM7, bool DEBUG, bool QB, bool LQ>
 hipError_t launch_l(const AttnArgs& a, hipStream_t s) {
-  const dim3 grid((a.Npad + kBlockM - 1) / kBlockM, a.BH);
-  hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ>), grid, dim3(kThreads), 0, s, a);
+  const int total = (a.Npad + kBlockM - 1) / kBlockM * a.BH;
+  TilePlan p{total, 0};
+  if (KV == 128) p = plan_tiles(total);
+  if (p.plain) hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ>), dim3(p.plain), dim3(kThreads), 0, s, a);
+  if constexpr (KV == 128) {
+    if (p.split)
+      hipLaunchKernelGGL((k_attn_e2m3_split<KTOK, SYM7, DEBUG, QB, LQ>), dim3(4 * p.split), dim3(kSplitThreads), 0, s, a,
+                         p.plain);
+  }
   return hipGetLastError();
 }
 

@@ -11,15 +11,18 @@
 
 namespace ra {
 
+// Linear launch index -> index in a list of total tiles.  A bijection for any
+// total: XCD x owns q + (x < r) consecutive tiles, q = total / 8, r = total % 8.
+__device__ __forceinline__ int xcd_order(int lin, int total) {
+  const int q = total >> 3, r = total & 7, x = lin & 7, k = lin >> 3;
+  return x * q + (x < r ? x : r) + k;
+}
+
 // Linear launch index -> (head bh, query tile) for a grid of (ntile, nbh).
-// A bijection for any grid size: XCD x owns q + (x < r) consecutive tiles,
-// q = total / 8, r = total % 8.
 __device__ __forceinline__ void xcd_tile(int& bh, int& tile) {
   const int ntile = static_cast<int>(gridDim.x);
-  const int total = ntile * static_cast<int>(gridDim.y);
-  const int lin = static_cast<int>(blockIdx.x) + ntile * static_cast<int>(blockIdx.y);
-  const int q = total >> 3, r = total & 7, x = lin & 7, k = lin >> 3;
-  const int L = x * q + (x < r ? x : r) + k;
+  const int L = xcd_order(static_cast<int>(blockIdx.x) + ntile * static_cast<int>(blockIdx.y),
+                          ntile * static_cast<int>(gridDim.y));
   bh = L / ntile;
   tile = L - bh * ntile;
 }

@@ -1,0 +1,88 @@
+"""The 256-query tiles of a FP6 attention call are divided between the plain
+kernel and the key-split one by their number (kv_block 128): a last round of
+at most 128 tiles on 256 compute units runs split.  The small parity cases all
+fall to the split kernel; here the plain kernel runs at the same small sizes
+(129 to 256 tiles), both together (257 and more), and the counts on either
+side of the line, with the options that have instantiations of their own.
+Sampled heads, among them those at the border, against the oracle: S and the
+running maxima bit for bit, P codes outside the tie band bit for bit, O within
+2e-3 of its largest value.
+"""
+import numpy as np
+import pytest
+
+import pcode_check
+from test_gpu_int4 import FORMATS, O_TOL, _cfg, _geo, _inputs, _params, _ra, _run_quant, _torch
+
+pytestmark = pytest.mark.gpu
+
+# heads, grid, case (rotation, q_group, k_group, v_group, kv_block, P mapping, smoothing, V Hadamard, l from codes)
+PLANS = [
+    (128, (1, 3, 5), (1, 128, 128, 128, 128, 0, 3, 0, 0)),     # 128 tiles: all split
+    (129, (1, 3, 43), (1, 128, 128, 128, 128, 0, 3, 0, 0)),    # 129: all plain, two blocks, the second of one key
+    (65, (3, 10, 10), (1, 1, 1, 128, 128, 0, 7, 0, 0)),        # 130 plain, per-token scales with the key bias
+    (130, (1, 8, 16), (2, 128, 32, 256, 128, 1, 3, 0, 1)),     # one full block, SYM7, l from the codes
+    (86, (5, 7, 11), (1, 128, 128, 128, 128, 0, 7, 1, 0)),     # 172 plain, four blocks, key bias, V Hadamard
+    (129, (1, 1, 257), (2, 1, 16, 128, 128, 0, 3, 0, 0)),      # 258: 256 plain, 2 split (the last head)
+    (257, (1, 8, 8), (1, 128, 64, 128, 128, 0, 3, 0, 0)),      # 256 plain, 1 split, half a block of keys
+    (130, (1, 15, 25), (3, 1, 128, 1 << 20, 128, 0, 4, 0, 0)), # 260, V scales per channel, Q smoothing alone
+]
+
+
+def _check(ora, w, case, heads, q, k, v):
+    torch, ra = _torch(), _ra()
+    rot, qg, kg, vg, kv, pq, sm, vrot, lq = case
+    p = _params(ra, w, rot, qg, kg, vg, kv, pq, sm, fmt=FORMATS["e2m3"], vrot=vrot, lq=lq)
+    bufs, _, _ = _run_quant(torch, ra, p, q, k, v)
+    geo, cfg = _geo(ora, w), _cfg(ora, rot, qg, kg, vg, kv, pq, sm, vrot, lq)
+    N, nb = w.N, -(-w.N // kv)
+    args = (bufs["q_codes"], bufs["q_scale"], bufs["k_codes"], bufs["k_scale"], bufs["v_codes"], bufs["v_scale"],
+            bufs["mu_v"] if sm & 2 else None)
+    kb = bufs["k_bias"] if sm & 4 else None
+    plain = torch.full((w.B * w.H, N, 128), float("nan"), dtype=torch.float32, device="cuda")
+    ra.attn_int4(p, *args, plain, k_bias=kb)
+    torch.cuda.synchronize()
+    assert torch.isfinite(plain).all()          # every row was written
+    s_d = torch.zeros((N, N), dtype=torch.int32, device="cuda")
+    u_d = torch.zeros((N, N), dtype=torch.uint8, device="cuda")
+    m_d = torch.zeros((N, nb), dtype=torch.float32, device="cuda")
+    o = torch.empty_like(plain)
+    for bh in heads:
+        ra.attn_int4_debug(p, *args, o, bh, 0, N, s_d, u_d, m_d, k_bias=kb)
+        torch.cuda.synchronize()
+        ref, d = ora.fwd_int4_head(geo, cfg, q[0, bh], k[0, bh], v[0, bh], dumps=True)
+        assert np.array_equal(s_d.cpu().numpy(), d["S"])
+        assert np.all(m_d.cpu().numpy() == d["m"])
+        pcode_check.compare(u_d.cpu().numpy(), d, pq, kv, N, label=f"{w.H}x{N} bh={bh}")
+        assert np.abs(plain[bh].cpu().numpy() - ref).max() / np.abs(ref).max() <= O_TOL
+    assert torch.equal(plain, o)
+
+
+@pytest.mark.parametrize("plan", range(len(PLANS)))
+def test_plain_and_split_tiles(ora, plan):
+    from paper_2607_02584_amd import datagen as dg
+    H, (T, Hg, W), case = PLANS[plan]
+    print(f"[tile plan] H={H} grid={T}x{Hg}x{W} case={case}", flush=True)
+    w = dg.small_workload(f"plan{plan}", T, Hg, W, H=H, seed=80 + plan)
+    _check(ora, w, case, sorted({0, min(127, H - 1), H - 2, H - 1}), *_inputs(w))
+
+
+@pytest.mark.parametrize("heads,kv", [(1, 128), (130, 128), (1, 64)])
+def test_wholly_masked_chunk_has_no_maximum(ora, heads, kv):
+    """Fewer tokens than one 32-key chunk with K scales per 32 keys: the other
+    chunks' groups hold no token and have scale 0.  With every score negative
+    the running maximum is negative, not the 0 that scale would give."""
+    from paper_2607_02584_amd import datagen as dg
+    print(f"[masked chunk] H={heads} kv={kv}", flush=True)
+    w = dg.small_workload("masked", 1, 3, 5, H=heads, seed=95)
+    q, k, v = _inputs(w)
+    x = np.random.default_rng(3).uniform(1.0, 2.0, size=(1, heads, 1, 128)).astype(np.float32)
+    small = np.random.default_rng(4).uniform(0.9, 1.1, size=q.shape).astype(np.float32)
+    q, k = dg.f32_to_bf16_bits(x * small), dg.f32_to_bf16_bits(-x * small)
+    # the positions turn by small angles only (theta large, extents small) along
+    # the pairs that carry the product, so it stays negative; the oracle confirms
+    case = (0, 128, 32, 128, kv, 0, 0, 0, 0)
+    geo, cfg = _geo(ora, w), _cfg(ora, 0, 128, 32, 128, kv, 0, 0)
+    _, d = ora.fwd_int4_head(geo, cfg, q[0, 0], k[0, 0], v[0, 0], dumps=True)
+    assert d["m"].max() < 0
+    _check(ora, w, case, [0, heads - 1], q, k, v)
