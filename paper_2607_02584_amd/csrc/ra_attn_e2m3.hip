@@ -494,40 +494,91 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
     if (++vr == a.v_bpg) vr = 0;
     float4 rr = make_float4(1.f, 1.f, 1.f, 1.f);
     if (vchange) rr = *reinterpret_cast<const float4*>(&sR[buf][4 * j]);
+    const float rt[4] = {rr.x, rr.y, rr.z, rr.w};
+    auto vratio = [&](int mt, int r) { of[mt][r] = __fmul_rn(of[mt][r], rt[mt]); };
+    if constexpr (!KTOK) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      of[0][r] = __fmul_rn(of[0][r], rr.x);
-      of[1][r] = __fmul_rn(of[1][r], rr.y);
-      of[2][r] = __fmul_rn(of[2][r], rr.z);
-      of[3][r] = __fmul_rn(of[3][r], rr.w);
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) vratio(mt, r);
     }
 
     // ---- block row maximum of fl(S * c) (c >= 0, so it is fl(max S * c);
     //      a fully masked chunk gives the seed of chunk_max, far below) ----
     float cch[NCH];
     float tmax = -INFINITY;
-    if (QB) {
-      // t = fma(S, c, bias) in place of S; the maximum is over t
+    if constexpr (KTOK) {
+      // Per-key values from LDS, 8 keys (two 16-byte reads of each kind) at a
+      // time and kDepth such units ahead: read where they are used, every pair
+      // of reads was waited for on its own (about 100 cycles, 8 times a block
+      // and by both waves of the SIMD at once).  With Q smoothing t = fma(S, c,
+      // bias) takes S's place and the maximum is over t.
+      constexpr int NU = 2 * NCH;   // units of 8 score registers
+      constexpr int kDepth = QB ? 2 : 3;
+      float4 kk[kDepth][2], bb[kDepth][2];
+      auto fetch = [&](int u) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int kl = (u >> 1) * 32 + 8 * (2 * (u & 1) + i) + 4 * hh;
+          kk[u % kDepth][i] = *reinterpret_cast<const float4*>(&sKs[buf][kl]);
+          if (QB) bb[u % kDepth][i] = *reinterpret_cast<const float4*>(&sB[buf][kl]);
+        }
+      };
+#pragma unroll
+      for (int u = 0; u < kDepth - 1; ++u) fetch(u);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if (u + kDepth - 1 < NU) fetch(u + kDepth - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const int ch = u >> 1;
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float4 k4 = kk[u % kDepth][i], b4 = bb[u % kDepth][i];
+          const float ka[4] = {k4.x, k4.y, k4.z, k4.w}, ba[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = 8 * (u & 1) + 4 * i + e;
+            const float c = __fmul_rn(cq, ka[e]);
+            float t;
+            if (QB) {
+              t = __fmaf_rn(s[ch][r], c, ba[e]);
+              if (MASKED && s[ch][r] == -INFINITY) t = -INFINITY;
+              s[ch][r] = t;
+            } else {
+              t = __fmul_rn(s[ch][r], c);
+            }
+            mx = fmaxf(mx, t);
+          }
+        }
+        tmax = fmaxf(tmax, mx);
+        // the V-ratio multiplies in equal parts, one per unit
+#pragma unroll
+        for (int i = 0; i < 64; ++i)
+          if (i / (64 / NU) == u) vratio(i >> 4, i & 15);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if constexpr (QB) {
+      // t = fma(S, c, bias) in place of S; the maximum is over t.  (The bias
+      // values read ahead as above were slower here: 3.54 against 3.46 ms.)
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
-        if (!KTOK) cch[ch] = __fmul_rn(cq, sKc[buf][ch]);
+        cch[ch] = __fmul_rn(cq, sKc[buf][ch]);
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-          const int kl = ch * 32 + 8 * r4 + 4 * hh;
-          const float4 b4 = *reinterpret_cast<const float4*>(&sB[buf][kl]);
+          const float4 b4 = *reinterpret_cast<const float4*>(&sB[buf][ch * 32 + 8 * r4 + 4 * hh]);
           const float bb[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int r = 4 * r4 + e;
-            const float c = KTOK ? __fmul_rn(cq, sKs[buf][kl + e]) : cch[ch];
-            float t = __fmaf_rn(s[ch][r], c, bb[e]);
+            float t = __fmaf_rn(s[ch][r], cch[ch], bb[e]);
             if (MASKED && s[ch][r] == -INFINITY) t = -INFINITY;
             s[ch][r] = t;
             tmax = fmaxf(tmax, t);
           }
         }
       }
-    } else if (!KTOK && a.k_group >= KV) {
+    } else if (a.k_group >= KV) {
       // one K scale for the whole block: a single product after the maximum
       float mx = chunk_max(s[0]);
 #pragma unroll
@@ -536,7 +587,7 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) cch[ch] = c0;
       tmax = __fmul_rn(mx, c0);
-    } else if (!KTOK) {
+    } else {
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
         cch[ch] = __fmul_rn(cq, sKc[buf][ch]);
@@ -545,14 +596,12 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
         // scale group holds no token: the product would be a zero score)
         if (!MASKED || mx > -3.0e38f) tmax = fmaxf(tmax, __fmul_rn(mx, cch[ch]));
       }
-    } else {
+    }
+    // the scales of the first two chunks' keys, read under the maximum's chain
+    float4 kp[2][4];
+    if constexpr (KTOK && !QB) {
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kl = ch * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-          tmax = fmaxf(tmax, __fmul_rn(s[ch][r], __fmul_rn(cq, sKs[buf][kl])));
-        }
+      for (int i = 0; i < 4; ++i) kp[0][i] = *reinterpret_cast<const float4*>(&sKs[buf][8 * i + 4 * hh]);
     }
     tmax = max_halves(tmax);
     const float mnew = fmaxf(m, tmax);
@@ -598,7 +647,8 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
           P = __builtin_amdgcn_exp2f(__fsub_rn(s[ch][r], mq));
         } else {
           float c;
-          if (KTOK) c = __fmul_rn(cq, sKs[buf][ch * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)]);
+          if (KTOK && ch < 2) c = __fmul_rn(cq, (&kp[ch][r >> 2].x)[r & 3]);
+          else if (KTOK) c = __fmul_rn(cq, sKs[buf][ch * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)]);
           else c = cch[ch];
           P = __builtin_amdgcn_exp2f(__fmaf_rn(s[ch][r], c, -mq));
         }
@@ -641,6 +691,11 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
       }
     };
 
+    if constexpr (KTOK && !QB) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kp[1][i] = *reinterpret_cast<const float4*>(&sKs[buf][32 + 8 * i + 4 * hh]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     read_vrecs(0);
 #pragma unroll
     for (int q = 0; q < 8; ++q) probs4(q >> 2, q & 3);
