@@ -17,6 +17,7 @@
 //   Q, K: (((c*8 + ch/16)*2 + (ch/8)%2)*32 + r)*8 + ch%8
 //   V:    (((c*2 + s)*2 + h)*128 + ch)*8 + e  holds V[32c + 16s + 8(e/4) + 4h + e%4][ch]
 #include <type_traits>
+#include <utility>
 
 #include "ra_internal.h"
 #include "ra_xcd.h"
@@ -47,55 +48,101 @@ __device__ __forceinline__ int fdiv(int n, int d, float inv_d) {
   return q;
 }
 
-// One thread per (token, 4 channels): RoPE in binary32, rounded to 16 bits,
-// written to the tiled layout.  Grid: (Npad/8, BH), 256 threads = 8 tokens.
-__global__ __launch_bounds__(256) void k_rope16(RopeTables t, const uint16_t* x, uint16_t* out, int N, int Npad,
-                                                int is_fp16) {
-  const int bh = blockIdx.y;
-  const int n = blockIdx.x * 8 + (threadIdx.x >> 5);
-  const int cl = threadIdx.x & 31;
-  uint16_t res[4] = {0, 0, 0, 0};
-  if (n < N) {
-    const uint2 w = *reinterpret_cast<const uint2*>(x + (static_cast<size_t>(bh) * N + n) * kD + 4 * cl);
-    const float xv[4] = {h2f(w.x & 0xffff, is_fp16), h2f(w.x >> 16, is_fp16), h2f(w.y & 0xffff, is_fp16),
-                         h2f(w.y >> 16, is_fp16)};
-    const int W = t.grid[2], Hg = t.grid[1];
-    const int tq = fdiv(n, W * Hg, 1.0f / static_cast<float>(W * Hg));
-    const int rem = n - tq * W * Hg;
-    const int hq = fdiv(rem, W, 1.0f / static_cast<float>(W));
-    const int pos[3] = {tq, hq, rem - hq * W};
+// One workgroup per 32-token chunk and group of heads: plain RoPE of Q and K in
+// binary32, rounded to 16 bits, written to the tiled layout.  A thread holds two
+// 16-byte pieces of the chunk (8 channels of one token each) and the cosines and
+// sines of their pairs, which do not depend on the head: it reads them once and
+// turns the same piece of every head's Q and K with them (read per head, as one
+// 16-byte table entry per pair, the tables were four times the bytes of the
+// data, from the L2).  The plain RoPE block is [c s; -s c], so the first half of
+// a table entry is all of it.  Global accesses are whole 256-byte rows on one
+// side and the chunk's 8 KB in order on the other; the piece (token r, channels
+// 8 u ..) passes through LDS slot 32 u + (r ^ u), which spreads the 16 pieces of
+// a row over the banks.  32760 tokens, 12 heads, Q and K together: 133 -> 67 us
+// (6 TB/s).
+__global__ __launch_bounds__(256) void k_rope16(RopeTables t, const uint16_t* q, const uint16_t* k, uint16_t* qo,
+                                                uint16_t* ko, int BH, int N, int Npad, int is_fp16, int heads) {
+  __shared__ __align__(16) uint4 tile[2][512];
+  const int c = blockIdx.x, tid = threadIdx.x;
+  const int h0 = blockIdx.y * heads, nh = BH - h0 < heads ? BH - h0 : heads;
+  const int u = tid & 15;          // channels 8 u .. 8 u + 7 of rows tid / 16 and 16 + tid / 16
+  const int W = t.grid[2], Hg = t.grid[1];
+  const int np0 = t.split[0] / 2, np1 = t.split[1] / 2, np2 = t.split[2] / 2;
+  float2 cs[2][4];
+  size_t src[2];
+  bool in[2];
+  int slot[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int p = 2 * cl + i;
-      int first = 0, a = 2;
-      for (int ax = 0; ax < 3; ++ax) {
-        const int np = t.split[ax] / 2;
-        if (p < first + np) {
-          a = ax;
-          break;
-        }
-        first += np;
-      }
-      const float4 g = t.axis[a][pos[a] * (t.split[a] / 2) + (p - first)];
-      const float y0 = __fmaf_rn(xv[2 * i + 1], g.z, __fmul_rn(xv[2 * i], g.x));
-      const float y1 = __fmaf_rn(xv[2 * i + 1], g.w, __fmul_rn(xv[2 * i], g.y));
-      res[2 * i] = f2h(y0, is_fp16);
-      res[2 * i + 1] = f2h(y1, is_fp16);
+  for (int i = 0; i < 2; ++i) {
+    const int r = 16 * i + (tid >> 4), n = 32 * c + r;
+    in[i] = n < N;
+    const int nn = in[i] ? n : N - 1;
+    src[i] = static_cast<size_t>(nn) * kD + 8 * u;
+    slot[i] = 32 * u + (r ^ u);
+    const int tq = fdiv(nn, W * Hg, 1.0f / static_cast<float>(W * Hg));
+    const int rem = nn - tq * W * Hg;
+    const int hq = fdiv(rem, W, 1.0f / static_cast<float>(W));
+    const int wq = rem - hq * W;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int p = 4 * u + e;
+      const float4* g = p < np0 ? t.axis[0] + tq * np0 + p
+                                : (p < np0 + np1 ? t.axis[1] + hq * np1 + (p - np0)
+                                                 : t.axis[2] + wq * np2 + (p - np0 - np1));
+      cs[i][e] = *reinterpret_cast<const float2*>(g);
     }
   }
-  if (n < Npad) {
-    const int c = n >> 5, r = n & 31, ch = 4 * cl;
-    const size_t off = static_cast<size_t>(bh) * Npad * kD +
-                       ((static_cast<size_t>(c * 8 + (ch >> 4)) * 2 + ((ch >> 3) & 1)) * 32 + r) * 8 + (ch & 7);
-    *reinterpret_cast<uint2*>(out + off) =
-        make_uint2(res[0] | (static_cast<uint32_t>(res[1]) << 16), res[2] | (static_cast<uint32_t>(res[3]) << 16));
+  auto base = [&](int job) {   // job 2 h + (0 for Q, 1 for K)
+    return ((job & 1) ? k : q) + static_cast<size_t>(h0 + (job >> 1)) * N * kD;
+  };
+  uint4 raw[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) raw[i] = *reinterpret_cast<const uint4*>(base(0) + src[i]);
+  for (int job = 0; job < 2 * nh; ++job) {
+    uint4* tl = tile[job & 1];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t w[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
+      uint32_t o[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x0 = h2f(w[e] & 0xffff, is_fp16), x1 = h2f(w[e] >> 16, is_fp16);
+        const float y0 = __fmaf_rn(x1, -cs[i][e].y, __fmul_rn(x0, cs[i][e].x));
+        const float y1 = __fmaf_rn(x1, cs[i][e].x, __fmul_rn(x0, cs[i][e].y));
+        o[e] = in[i] ? f2h(y0, is_fp16) | (static_cast<uint32_t>(f2h(y1, is_fp16)) << 16) : 0u;
+      }
+      tl[slot[i]] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+    if (job + 1 < 2 * nh) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) raw[i] = *reinterpret_cast<const uint4*>(base(job + 1) + src[i]);
+    }
+    __syncthreads();   // two tiles: the next write goes to the other one
+    uint4* dst = reinterpret_cast<uint4*>(((job & 1) ? ko : qo) +
+                                          (static_cast<size_t>(h0 + (job >> 1)) * Npad + 32 * c) * kD);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int x = 256 * i + tid;   // slot 32 u' + r'
+      dst[x] = tl[(x & ~31) + ((x & 31) ^ (x >> 5))];
+    }
   }
 }
 
-// V relayout: one workgroup per 32-token chunk; the chunk goes through LDS.
-__global__ __launch_bounds__(256) void k_v16_relayout(const uint16_t* v, uint16_t* out, int N, int Npad) {
+// The table copy (the first `copy_blocks` workgroups; src may be pinned host
+// memory read through its device mapping) and the V relayout, which needs no
+// tables: one workgroup per 32-token chunk and head, the chunk through LDS.
+__global__ __launch_bounds__(256) void k_v16_relayout(const uint32_t* tsrc, uint32_t* tdst, int nwords,
+                                                      int copy_blocks, const uint16_t* v, uint16_t* out, int N,
+                                                      int Npad) {
   __shared__ uint16_t tile[32][kD + 2];
-  const int bh = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
+  if (static_cast<int>(blockIdx.x) < copy_blocks) {
+    const int i = blockIdx.x * 256 + tid;
+    if (i < nwords) tdst[i] = tsrc[i];
+    return;
+  }
+  const int nc = Npad / 32, x = blockIdx.x - copy_blocks;
+  const int bh = x / nc, c = x - bh * nc;
   for (int i = tid; i < 32 * 32; i += 256) {
     const int r = i >> 5, cl = i & 31;
     const int n = c * 32 + r;
@@ -394,14 +441,20 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
 
 }  // namespace
 
-hipError_t launch_rope16(const RopeTables& t, const uint16_t* x, uint16_t* out, int BH, int N, int Npad, int is_fp16,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_rope16, dim3(Npad / 8, BH), dim3(256), 0, s, t, x, out, N, Npad, is_fp16);
-  return hipGetLastError();
-}
-
-hipError_t launch_v16_relayout(const uint16_t* v, uint16_t* out, int BH, int N, int Npad, hipStream_t s) {
-  hipLaunchKernelGGL(k_v16_relayout, dim3(Npad / 32, BH), dim3(256), 0, s, v, out, N, Npad);
+hipError_t launch_prepare16(const RopeTables& t, const uint32_t* tsrc, uint32_t* tdst, int64_t nwords,
+                            const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* qo, uint16_t* ko,
+                            uint16_t* vo, int BH, int N, int Npad, int is_fp16, hipStream_t s) {
+  const int copy_blocks = static_cast<int>((nwords + 255) / 256);
+  hipLaunchKernelGGL(k_v16_relayout, dim3(copy_blocks + Npad / 32 * BH), dim3(256), 0, s, tsrc, tdst,
+                     static_cast<int>(nwords), copy_blocks, v, vo, N, Npad);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // 4 heads per workgroup, or fewer while that leaves under 4 workgroups per
+  // compute unit, where a workgroup's chain of heads is what takes the time
+  int heads = 4;
+  while (heads > 1 && static_cast<int64_t>(Npad / 32) * ((BH + heads - 1) / heads) < 1024) heads /= 2;
+  hipLaunchKernelGGL(k_rope16, dim3(Npad / 32, (BH + heads - 1) / heads), dim3(256), 0, s, t, q, k, qo, ko, BH, N,
+                     Npad, is_fp16, heads);
   return hipGetLastError();
 }
 

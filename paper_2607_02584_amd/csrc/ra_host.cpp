@@ -304,9 +304,11 @@ struct TableCopy {
 };
 
 // Describes the tables of p, placed at dev (table_bytes(p) bytes of the
-// workspace), in *out, and copies them there on stream s -- or, with defer,
-// leaves the copy to the caller's next kernel and describes it in *defer.
-int put_tables(const ra_params* p, float* dev, hipStream_t s, ra::RopeTables* out, TableCopy* defer = nullptr) {
+// workspace), in *out, and in *copy the copy that brings them there, which the
+// caller's next kernel makes: it reads the pinned table through its device
+// mapping, so the copy stays on the kernel queue, with no hand-over to a copy
+// engine and back.
+int put_tables(const ra_params* p, float* dev, ra::RopeTables* out, TableCopy* copy) {
   const std::string key = table_key(p);
   std::lock_guard<std::mutex> lock(g_mu);
   auto it = g_tables.find(key);
@@ -323,16 +325,9 @@ int put_tables(const ra_params* p, float* dev, hipStream_t s, ra::RopeTables* ou
     it = g_tables.emplace(key, ht).first;
   }
   const HostTable& ht = it->second;
-  // a kernel on s reads the pinned table through its device mapping: the copy
-  // stays on the kernel queue, with no hand-over to a copy engine and back
-  if (defer) {
-    defer->src = reinterpret_cast<const uint32_t*>(ht.mapped);
-    defer->dst = reinterpret_cast<uint32_t*>(dev);
-    defer->nwords = static_cast<int64_t>(ht.bytes / 4);
-  } else {
-    RA_CHECK_HIP(ra::launch_copy_u32(reinterpret_cast<const uint32_t*>(ht.mapped), reinterpret_cast<uint32_t*>(dev),
-                                     static_cast<int64_t>(ht.bytes / 4), s));
-  }
+  copy->src = reinterpret_cast<const uint32_t*>(ht.mapped);
+  copy->dst = reinterpret_cast<uint32_t*>(dev);
+  copy->nwords = static_cast<int64_t>(ht.bytes / 4);
   *out = tables_at(p, dev, ht.off);
   return RA_OK;
 }
@@ -535,15 +530,12 @@ int fp16_prepare_impl(const ra_params* p, const void* q, const void* k, const vo
   ra_params plain = *p;
   plain.rotation = RA_ROT_NONE;
   plain.rot_blocks = nullptr;
-  int rc = put_tables(&plain, w.tables, s, &t);
+  TableCopy tc;
+  int rc = put_tables(&plain, w.tables, &t, &tc);
   if (rc) return rc;
-  const int is16 = p->in_dtype == RA_FP16;
-  RA_CHECK_HIP(ra::launch_rope16(t, static_cast<const uint16_t*>(q), w.q, static_cast<int>(z.BH), p->N,
-                                 static_cast<int>(z.Npad), is16, s));
-  RA_CHECK_HIP(ra::launch_rope16(t, static_cast<const uint16_t*>(k), w.k, static_cast<int>(z.BH), p->N,
-                                 static_cast<int>(z.Npad), is16, s));
-  RA_CHECK_HIP(ra::launch_v16_relayout(static_cast<const uint16_t*>(v), w.v, static_cast<int>(z.BH), p->N,
-                                       static_cast<int>(z.Npad), s));
+  RA_CHECK_HIP(ra::launch_prepare16(t, tc.src, tc.dst, tc.nwords, static_cast<const uint16_t*>(q),
+                                    static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), w.q, w.k, w.v,
+                                    static_cast<int>(z.BH), p->N, static_cast<int>(z.Npad), p->in_dtype == RA_FP16, s));
   return RA_OK;
 }
 
@@ -695,7 +687,7 @@ int rotate_attn_quantize_qk(const ra_params* p, const void* q, const void* k, ui
   const Int4Ws w = carve_int4(p, workspace);
   ra::RopeTables t;
   TableCopy tc;
-  if ((rc = put_tables(p, w.tables, st(stream), &t, &tc))) return rc;
+  if ((rc = put_tables(p, w.tables, &t, &tc))) return rc;
   ProdOut out;
   out.qc = q_codes;
   out.qs = q_scale;
@@ -737,7 +729,7 @@ int rotate_attn_quantize_qkv(const ra_params* p, const void* q, const void* k, c
   const Int4Ws w = carve_int4(p, workspace);
   ra::RopeTables t;
   TableCopy tc;
-  if ((rc = put_tables(p, w.tables, st(stream), &t, &tc))) return rc;
+  if ((rc = put_tables(p, w.tables, &t, &tc))) return rc;
   ProdOut out;
   out.qc = q_codes;
   out.qs = q_scale;
@@ -791,7 +783,7 @@ int rotate_attn_fwd_int4(const ra_params* p, const void* q, const void* k, const
   const Int4Ws w = carve_int4(p, workspace);
   ra::RopeTables t;
   TableCopy tc;
-  if ((rc = put_tables(p, w.tables, st(stream), &t, &tc))) return rc;
+  if ((rc = put_tables(p, w.tables, &t, &tc))) return rc;
   return int4_forward(p, t, tc, q, k, v, o, w, st(stream));
 }
 

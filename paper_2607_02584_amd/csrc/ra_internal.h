@@ -128,7 +128,6 @@ struct Prologue {
 // ---- launchers (return hipError_t) ----
 hipError_t launch_pass(const RopeTables& t, const PassArgs& pa, hipStream_t s);
 hipError_t launch_prologue(const Prologue& pr, hipStream_t s);
-hipError_t launch_copy_u32(const uint32_t* src, uint32_t* dst, int64_t n, hipStream_t s);
 // n host floats -> dst on the device, carried in kernel arguments (no allocation)
 hipError_t launch_write_floats(const float* host, size_t n, float* dst, hipStream_t s);
 hipError_t launch_attn_int4(const AttnArgs& a, int kv_block, bool k_per_token, bool sym7, bool debug,
@@ -138,9 +137,11 @@ hipError_t launch_attn_e2m3(const AttnArgs& a, int kv_block, bool k_per_token, b
 hipError_t launch_attn_e2m3_debug(const AttnArgs& a, int kv_block, bool k_per_token, bool sym7, hipStream_t s);
 // (both launchers pick the key-bias variant when a.kbias is set and the
 // quantized-normaliser variant when a.lq is set)
-hipError_t launch_rope16(const RopeTables& t, const uint16_t* x, uint16_t* out, int BH, int N, int Npad,
-                         int is_fp16, hipStream_t s);
-hipError_t launch_v16_relayout(const uint16_t* v, uint16_t* out, int BH, int N, int Npad, hipStream_t s);
+// the fallback's producer: nwords of RoPE tables from tsrc to tdst (which t
+// describes), Q and K after RoPE and V in the 16-bit tiled layouts
+hipError_t launch_prepare16(const RopeTables& t, const uint32_t* tsrc, uint32_t* tdst, int64_t nwords,
+                            const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* qo, uint16_t* ko,
+                            uint16_t* vo, int BH, int N, int Npad, int is_fp16, hipStream_t s);
 hipError_t launch_attn_fp16(const Fp16Args& a, int kv_block, hipStream_t s);
 
 }  // namespace ra
