@@ -150,6 +150,29 @@ __device__ __forceinline__ void rescale_group(v16f (&o)[4], float ab, unsigned l
   rescale_row<4 * G + 3>(o, ab, moved);
 }
 
+// The same by register moves (row_factors): the key-split kernel, one wave per
+// SIMD on its own chain, waited for every swizzle (1024 tokens, 2 heads: 37.2 ->
+// 35.8 us); the plain kernel's other wave covers that wait, and there the
+// swizzles, one instruction where the DPP moves take issue slots, stay
+// (14787 tokens, Q smoothing: 1.957 ms against 1.969 ms).
+template <int R>
+__device__ __forceinline__ void rescale_row_dpp(v16f (&o)[4], const RowFactors& alpha, unsigned long long moved) {
+  constexpr int q0 = 8 * (R >> 2) + (R & 3);
+  if ((moved >> q0) & 0x11ull) {
+    const float ar = row_factor<R>(alpha);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) o[mt][R] = __fmul_rn(o[mt][R], ar);
+  }
+}
+template <int G>
+__device__ __forceinline__ void rescale_group_dpp(v16f (&o)[4], const RowFactors& alpha, unsigned long long moved) {
+  if (!((moved >> (8 * G)) & 0xFFull)) return;
+  rescale_row_dpp<4 * G>(o, alpha, moved);
+  rescale_row_dpp<4 * G + 1>(o, alpha, moved);
+  rescale_row_dpp<4 * G + 2>(o, alpha, moved);
+  rescale_row_dpp<4 * G + 3>(o, alpha, moved);
+}
+
 // 24-byte record -> operand registers (6 used dwords).  The fences keep the
 // three reads apart: merged into paired reads, whose offset field stops at
 // 2 KiB, the records of a tile would each need an address add, while single
@@ -1044,12 +1067,11 @@ __global__ __launch_bounds__(kSplitThreads, DEBUG ? 1 : 2) void k_attn_e2m3_spli
     }
     const unsigned long long moved = __ballot(alpha != 1.0f);
     if (moved) {
-      const float ab = __int_as_float(
-          __builtin_amdgcn_update_dpp(__float_as_int(alpha), __float_as_int(alpha), 0x12C, 0xC, 0xF, false));
-      rescale_group<0>(of, ab, moved);
-      rescale_group<1>(of, ab, moved);
-      rescale_group<2>(of, ab, moved);
-      rescale_group<3>(of, ab, moved);
+      const RowFactors ab = row_factors(alpha);
+      rescale_group_dpp<0>(of, ab, moved);
+      rescale_group_dpp<1>(of, ab, moved);
+      rescale_group_dpp<2>(of, ab, moved);
+      rescale_group_dpp<3>(of, ab, moved);
     }
     float ls[4];
 #pragma unroll

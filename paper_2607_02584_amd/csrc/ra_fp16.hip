@@ -198,38 +198,48 @@ __device__ __forceinline__ uint32_t pack2(float x, float y) {
   return __builtin_bit_cast(uint32_t, t);
 }
 
+// f(0) .. f(15), each index a compile-time constant
+template <typename F, int... R>
+__device__ __forceinline__ void each16_(F&& f, std::integer_sequence<int, R...>) {
+  (f(std::integral_constant<int, R>()), ...);
+}
+template <typename F>
+__device__ __forceinline__ void each16(F&& f) {
+  each16_(f, std::make_integer_sequence<int, 16>());
+}
+
 template <typename V>
 __device__ __forceinline__ V as_vec(uint4 u) {
   return __builtin_bit_cast(V, u);
 }
 
-// K and V tiles move global -> registers -> LDS; each thread carries KV / 16
-// 16-byte pieces of each (the K and V pieces may belong to different blocks).
+// A tile of KV keys (K or V: KV * 256 bytes) from global memory straight into
+// LDS, in pieces of 1 KB (16 bytes per lane), every wave its share.  Issued from
+// asm, so the compiler does not wait for it at unrelated LDS accesses; dma_wait
+// and a barrier make the data visible.
 template <int KV>
-struct Tile16 {
-  typedef unsigned T __attribute__((ext_vector_type(4)));
-  static constexpr int NP = KV / 16;
-  static_assert(NP * 16 * 256 == KV * kD * 2, "pieces cover the tile");
-  T k[NP], v[NP];
-  __device__ __forceinline__ void load(const uint16_t* kg, const uint16_t* vg, int tid) {
-    const T* K = reinterpret_cast<const T*>(kg) + tid;
-    const T* V = reinterpret_cast<const T*>(vg) + tid;
+__device__ __forceinline__ void dma_tile(const uint16_t* src, uint16_t* dst, int wave, int lane) {
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      k[i] = K[256 * i];
-      v[i] = V[256 * i];
-    }
+  for (int i = 0; i < KV / 16; ++i) {
+    const int o = (i * 4 + wave) * 512;   // elements
+    const void* g = src + o + 8 * lane;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const unsigned l =
+        static_cast<unsigned>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint16_t*)(dst + o)));
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :
+                 : "v"(g), "s"(__builtin_amdgcn_readfirstlane(l))
+                 : "m0", "memory");
+#else
+    (void)g;
+#endif
   }
-  __device__ __forceinline__ void store(uint16_t* ks, uint16_t* vs, int tid) const {
-    T* K = reinterpret_cast<T*>(ks) + tid;
-    T* V = reinterpret_cast<T*>(vs) + tid;
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      K[256 * i] = k[i];
-      V[256 * i] = v[i];
-    }
-  }
-};
+}
+__device__ __forceinline__ void dma_wait() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+}
 
 // One wave = 32 queries; S^T = K Q^T puts the scores of one query in one lane
 // (register r of chunk ch is key 32 ch + 8 (r / 4) + 4 hh + r % 4).  The 16-bit
@@ -253,7 +263,7 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
   constexpr int TILE = kKV * kD;  // elements of K (and of V) per block
   __shared__ __align__(16) uint16_t sK[2][TILE];
   __shared__ __align__(16) uint16_t sV[2][TILE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hh = lane >> 5, j = lane & 31;
   int bh, qtile;
   xcd_tile(bh, qtile);
@@ -265,7 +275,8 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
   const uint16_t* kbase = a.k + hoff;
   const uint16_t* vbase = a.v + hoff;
   const float Kc = a.Kc;
-  auto blk = [&](int b) { return static_cast<size_t>(b < nblocks ? b : nblocks - 1) * TILE; };
+  auto load_k = [&](int b) { dma_tile<kKV>(kbase + static_cast<size_t>(b) * TILE, sK[b & 1], wave, lane); };
+  auto load_v = [&](int b) { dma_tile<kKV>(vbase + static_cast<size_t>(b) * TILE, sV[b & 1], wave, lane); };
 
   vec qop[8];
   {
@@ -286,13 +297,11 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
   };
   v16f s[NCH];
 
-  // prologue: K and V of block 0 and K of block 1 in LDS, block 0's scores;
-  // then V of block 1 and K of block 2 staged for the first step
-  Tile16<kKV> tp;
-  tp.load(kbase, vbase, tid);
-  tp.store(sK[0], sV[0], tid);
-  tp.load(kbase + blk(1), vbase + blk(1), tid);
-  tp.store(sK[1], sV[1], tid);
+  // prologue: K and V of block 0 and K of block 1 in LDS, block 0's scores
+  load_k(0);
+  load_v(0);
+  if (nblocks > 1) load_k(1);
+  dma_wait();
   __syncthreads();
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch)
@@ -302,7 +311,6 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
   for (int kc = 0; kc < 8; ++kc)
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) s[ch] = MF<F16>::mfma(kop(sK[0], ch, kc), qop[kc], s[ch]);
-  tp.load(kbase + blk(2), vbase + blk(1), tid);
   __syncthreads();   // every wave has read block 0's K before it is overwritten
 
   auto step = [&](int jb, auto masked_tag, auto more_tag) {
@@ -316,6 +324,12 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
     __builtin_amdgcn_s_setprio(1);
     const int buf = jb & 1;
     const int key0 = jb * kKV;
+    // block j + 2's K where block j's was, block j + 1's V where block j - 1's
+    // was: requested at the block's start, waited for at its end
+    if (more) {
+      if (jb + 2 < nblocks) load_k(jb + 2);
+      load_v(jb + 1);
+    }
     if (MASKED) {
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch)
@@ -325,29 +339,29 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
     }
 
     // ---- row maximum of S * Kc (Kc > 0: the product of the maximum) ----
-    float mx = fmaxf(fmaxf(s[0][0], s[0][1]), s[0][2]);
+    // (a chain of three-input maxima per chunk, seeded below every score)
+    float mx = -3.40282347e38f;
 #pragma unroll
-    for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, s[0][r]), s[0][r + 1]);
-    mx = fmaxf(mx, s[0][15]);
+    for (int ch = 0; ch < NCH; ++ch) {
+      float cx = -3.40282347e38f;
 #pragma unroll
-    for (int ch = 1; ch < NCH; ++ch)
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) mx = fmaxf(fmaxf(mx, s[ch][r]), s[ch][r + 1]);
-    float tmax = __fmul_rn(mx, Kc);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+      for (int r = 0; r < 16; r += 2) cx = fmaxf(fmaxf(cx, s[ch][r]), s[ch][r + 1]);
+      mx = fmaxf(mx, cx);
+    }
+    const float tmax = max_halves(__fmul_rn(mx, Kc));
     const float mnew = fmaxf(m, tmax);
     const float alpha = __builtin_amdgcn_exp2f(m - mnew);
     m = mnew;
     if (__any(alpha != 1.0f)) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float ar = __shfl(alpha, 8 * (r >> 2) + 4 * hh + (r & 3));
+      const RowFactors ab = row_factors(alpha);
+      auto row = [&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        const float ar = row_factor<r>(ab);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) of[mt][r] = __fmul_rn(of[mt][r], ar);
-      }
+      };
+      each16(row);
     }
-    // block j + 2's K where block j's was, block j + 1's V where block j - 1's was
-    tp.store(sK[buf], sV[buf ^ 1], tid);
 
     // ---- P = 2^(S Kc - m) in 16 bits, row sums of the unrounded P, O += P V ----
     float ls[4];
@@ -412,7 +426,7 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
       if (c == 0) __builtin_amdgcn_s_setprio(0);
     }
     l = __fmaf_rn(l, alpha, (ls[0] + ls[1]) + (ls[2] + ls[3]));
-    tp.load(kbase + blk(jb + 3), vbase + blk(jb + 2), tid);
+    if (more) dma_wait();
     __syncthreads();
   };
 

@@ -22,6 +22,28 @@ __device__ __forceinline__ float max_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// A per-query factor (lane q of each wave half holds query q's) for the output
+// rows of a 32x32 tile, whose register r is query 8 (r / 4) + 4 hh + r % 4 in
+// every lane of wave half hh.  `even` and `odd` hold the factors of the even
+// and of the odd row of 16 lanes of each half in both of its rows (the upper
+// half's moved down by 4 lanes first), so register r's factor is one lane of
+// each row, which a DPP row broadcast delivers: register moves only, where a
+// lane permute through LDS cost a round trip per output row.
+struct RowFactors {
+  float even, odd;
+};
+__device__ __forceinline__ RowFactors row_factors(float x) {
+  const int u = __float_as_int(x);
+  const unsigned b = static_cast<unsigned>(__builtin_amdgcn_update_dpp(u, u, 0x12C, 0xC, 0xF, false));  // row_ror:12
+  const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+template <int R>
+__device__ __forceinline__ float row_factor(const RowFactors& f) {
+  constexpr int lane = 8 * ((R >> 2) & 1) + (R & 3);
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(R < 8 ? f.even : f.odd), 0x150 + lane, 0xF, 0xF, true));
+}
+
 // RoPE/rotation tables on the device.  For axis a the table holds, for every
 // position pos in [0, extent_a) and pair k in [0, D_a/2), the binary32 2x2
 // block G = M (or M R for the merged interleaved rotation) as
