@@ -252,7 +252,7 @@ __device__ __forceinline__ void dma_wait() {
 // rounded to 16 bits, its score registers take the next block's scores of
 // the same chunk; those products and the chunk's PV products run on the
 // matrix core beside the next chunk's probabilities, with their LDS operands
-// read two products ahead, and a block starts with its scores in registers.
+// read four products ahead, and a block starts with its scores in registers.
 // K tiles are staged two blocks ahead and V tiles one block ahead, so two LDS
 // buffers of each suffice (block j + 2's K goes where block j's K was, whose
 // scores were taken during block j - 1).
@@ -407,21 +407,31 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
     };
 #pragma unroll
     for (int r2 = 0; r2 < 8; ++r2) probs(0, r2);
-    vec o0 = opB(0, 0), o1 = opB(0, 1);
+    // Operands are read from LDS kAhead products ahead, and every product is a
+    // scheduling region of its own: left alone, the compiler moved the reads
+    // back to one product before their use, and the matrix core waited for
+    // them (1560 tokens, 12 heads 52.1 -> 50.2 us, 4680 tokens, 5 heads 109 ->
+    // 104 us, 32760 tokens 6.09 -> 5.91 ms; 3, 6 or 8 ahead, or regions of two
+    // products: 0.3 to 1.5 % slower).
+    constexpr int kAhead = 4;
+    vec ops[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) ops[i] = opB(0, i);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       // chunk c's products, beside chunk c + 1's probabilities
 #pragma unroll
       for (int i = 0; i < NPR; ++i) {
-        // the operand two products ahead (into the next chunk's products)
-        const int n2 = i + 2;
+        // the operand kAhead products ahead (into the next chunk's products)
+        const int n2 = i + kAhead;
         const int c2 = n2 < NPR ? c : c + 1, i2 = n2 < NPR ? n2 : n2 - NPR;
-        const vec on = c2 < NCH ? opB(c2, i2) : o0;
-        product(c, i, o0);
-        o0 = o1;
-        o1 = on;
+        vec& op = ops[(c * NPR + i) % kAhead];
+        product(c, i, op);
+        if (c2 < NCH) op = opB(c2, i2);
         constexpr int PER = NPR / 8;   // products per pair of probabilities
         if (c + 1 < NCH && i % PER == PER - 1) probs(c + 1, i / PER);
+        __builtin_amdgcn_sched_barrier(0);
       }
       if (c == 0) __builtin_amdgcn_s_setprio(0);
     }
