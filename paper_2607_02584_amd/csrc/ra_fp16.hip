@@ -29,7 +29,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
-constexpr int kBlockM = 128;  // queries per workgroup
 
 __device__ __forceinline__ float h2f(uint16_t b, int is_fp16) {
   if (is_fp16) return __half2float(__ushort_as_half(b));
@@ -217,11 +216,11 @@ __device__ __forceinline__ V as_vec(uint4 u) {
 // LDS, in pieces of 1 KB (16 bytes per lane), every wave its share.  Issued from
 // asm, so the compiler does not wait for it at unrelated LDS accesses; dma_wait
 // and a barrier make the data visible.
-template <int KV>
+template <int KV, int NW>
 __device__ __forceinline__ void dma_tile(const uint16_t* src, uint16_t* dst, int wave, int lane) {
 #pragma unroll
-  for (int i = 0; i < KV / 16; ++i) {
-    const int o = (i * 4 + wave) * 512;   // elements
+  for (int i = 0; i < KV / (4 * NW); ++i) {
+    const int o = (i * NW + wave) * 512;   // elements
     const void* g = src + o + 8 * lane;
 #if defined(__HIP_DEVICE_COMPILE__)
     const unsigned l =
@@ -241,6 +240,35 @@ __device__ __forceinline__ void dma_wait() {
 #endif
 }
 
+// Output rows of a wave (register r of a tile: query 8 (r / 4) + 4 hh + r % 4 of
+// the 32 from q0 on), tiles T0 .. T0 + NT - 1, times inv[r], in the output type;
+// the type is chosen once, not per element.
+template <int T0, int NT, typename T, typename F>
+__device__ __forceinline__ void store_rows(T* o, const v16f (&of)[4], const float (&inv)[16], int N, int q0, int hh, F conv) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int qi = 8 * (r >> 2) + 4 * hh + (r & 3);
+    if (q0 + qi < N) {
+#pragma unroll
+      for (int mt = T0; mt < T0 + NT; ++mt) o[qi * kD + mt * 32] = conv(of[mt][r] * inv[r]);
+    }
+  }
+}
+template <int T0, int NT>
+__device__ __forceinline__ void finish_rows(const Fp16Args& a, const v16f (&of)[4], float ltot, int bh, int q0, int hh,
+                                            int j) {
+  float inv[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) inv[r] = 1.0f / __shfl(ltot, 8 * (r >> 2) + 4 * hh + (r & 3));
+  const size_t ob = (static_cast<size_t>(bh) * a.N + q0) * kD + j;
+  if (a.out_dtype == 2)
+    store_rows<T0, NT>(static_cast<float*>(a.o) + ob, of, inv, a.N, q0, hh, [](float v) { return v; });
+  else if (a.out_dtype == 1)
+    store_rows<T0, NT>(static_cast<uint16_t*>(a.o) + ob, of, inv, a.N, q0, hh, [](float v) { return f2h(v, 1); });
+  else
+    store_rows<T0, NT>(static_cast<uint16_t*>(a.o) + ob, of, inv, a.N, q0, hh, [](float v) { return f2h(v, 0); });
+}
+
 // One wave = 32 queries; S^T = K Q^T puts the scores of one query in one lane
 // (register r of chunk ch is key 32 ch + 8 (r / 4) + 4 hh + r % 4).  The 16-bit
 // P values of register pairs are directly the A operand of O = P V (A and B
@@ -256,8 +284,15 @@ __device__ __forceinline__ void dma_wait() {
 // K tiles are staged two blocks ahead and V tiles one block ahead, so two LDS
 // buffers of each suffice (block j + 2's K goes where block j's K was, whose
 // scores were taken during block j - 1).
-template <bool F16, int kKV>
-__global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
+// NW waves share the K/V tiles.  8 (256 queries) put two waves on every SIMD of a
+// compute unit with one copy of the tiles: at kv_block 128 the tiles fill the
+// LDS, and 4 waves were alone with it (32760 tokens 7.40 -> 5.88 ms); at
+// kv_block 64 the unit's tile traffic halves (6.17 -> 5.95 ms; the kernel runs at
+// the power limit there, 1.9 GHz).  4 (128 queries) are for a last round that
+// would leave units idle.  The launch covers the query tiles from the 256-query
+// tile tile0 of the list (head by head) on.
+template <bool F16, int kKV, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : (kKV == 64 ? 2 : 1)) void k_attn16(Fp16Args a, int tile0) {
   typedef typename MF<F16>::vec vec;
   constexpr int NCH = kKV / 32;
   constexpr int TILE = kKV * kD;  // elements of K (and of V) per block
@@ -265,9 +300,13 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
   __shared__ __align__(16) uint16_t sV[2][TILE];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hh = lane >> 5, j = lane & 31;
-  int bh, qtile;
-  xcd_tile(bh, qtile);
-  const int q0 = qtile * kBlockM + wave * 32;
+  constexpr int PER = 8 / NW;   // workgroups per 256-query tile
+  const int ntile = (a.Npad + 255) / 256;
+  const int U = PER * tile0 + xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+  const int bh = U / PER / ntile;
+  const int wq0 = (U / PER - bh * ntile) * 256 + (U % PER) * (32 * NW);
+  if (wq0 >= a.N) return;   // the last tile of a head may reach past its tokens
+  const int q0 = wq0 + wave * 32;
   const int qrow = q0 + j;
   const int N = a.N;
   const int nblocks = (N + kKV - 1) / kKV;
@@ -275,12 +314,15 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
   const uint16_t* kbase = a.k + hoff;
   const uint16_t* vbase = a.v + hoff;
   const float Kc = a.Kc;
-  auto load_k = [&](int b) { dma_tile<kKV>(kbase + static_cast<size_t>(b) * TILE, sK[b & 1], wave, lane); };
-  auto load_v = [&](int b) { dma_tile<kKV>(vbase + static_cast<size_t>(b) * TILE, sV[b & 1], wave, lane); };
+  auto load_k = [&](int b) { dma_tile<kKV, NW>(kbase + static_cast<size_t>(b) * TILE, sK[b & 1], wave, lane); };
+  auto load_v = [&](int b) { dma_tile<kKV, NW>(vbase + static_cast<size_t>(b) * TILE, sV[b & 1], wave, lane); };
 
   vec qop[8];
   {
-    const uint16_t* qp = a.q + hoff + static_cast<size_t>(qrow >> 5) * 4096 + (qrow & 31) * 8;
+    // (waves past the padded length, in the last workgroup, take the last rows
+    // and store nothing)
+    const int qr = qrow < a.Npad ? qrow : a.Npad - 32 + j;
+    const uint16_t* qp = a.q + hoff + static_cast<size_t>(qr >> 5) * 4096 + (qr & 31) * 8;
 #pragma unroll
     for (int kc = 0; kc < 8; ++kc) qop[kc] = as_vec<vec>(*reinterpret_cast<const uint4*>(qp + (kc * 2 + hh) * 256));
   }
@@ -446,20 +488,196 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16(Fp16Args a) {
   step(nblocks - 1, kYes(), kNo());
 
   // ---- epilogue: O / l ----
-  const float ltot = l + __shfl_xor(l, 32);
+  finish_rows<0, 4>(a, of, l + __shfl_xor(l, 32), bh, q0, hh, j);
+}
+
+// --------------------------------------------------- key-split variant --
+// The same rows by workgroups of 4 waves and 64 queries: wave (qs, kh) takes
+// queries 32 qs .. 32 qs + 31 and the half kh of every block's keys, so a
+// block's chain (maximum, alpha, probabilities, products) is half as long and a
+// 256-query tile becomes four workgroups.  The two waves of a row exchange the
+// maxima of their halves across the block barrier, each keeps its own row sums
+// and O over its keys, and both are added at the end.  The next block's scores
+// go to registers of their own and are taken beside the maximum's chain.
+template <bool F16, int kKV>
+__global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16_split(Fp16Args a, int tile0) {
+  typedef typename MF<F16>::vec vec;
+  constexpr int NCW = kKV / 64;   // 32-key chunks per wave
+  constexpr int TILE = kKV * kD;
+  __shared__ __align__(16) uint16_t sT[4 * TILE];   // K tiles of blocks j, j + 1 (j mod 2), then V
+  __shared__ float sM[2][4][32];
+  __shared__ float sL[4][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hh = lane >> 5, j = lane & 31;
+  const int qs = wave & 1, kh = wave >> 1;
+  const int ntile = (a.Npad + 255) / 256;
+  const int U = 4 * tile0 + xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+  const int bh = (U >> 2) / ntile;
+  const int wq0 = ((U >> 2) - bh * ntile) * 256 + (U & 3) * 64;
+  if (wq0 >= a.N) return;   // the last tile of a head may reach past its tokens
+  const int q0 = wq0 + 32 * qs, qrow = q0 + j;
+  const int N = a.N;
+  const int nblocks = (N + kKV - 1) / kKV;
+  const size_t hoff = static_cast<size_t>(bh) * a.Npad * kD;
+  const uint16_t* kbase = a.k + hoff;
+  const uint16_t* vbase = a.v + hoff;
+  const float Kc = a.Kc;
+  uint16_t* const sK = sT;
+  uint16_t* const sV = sT + 2 * TILE;
+  auto load_k = [&](int b) { dma_tile<kKV, 4>(kbase + static_cast<size_t>(b) * TILE, sK + (b & 1) * TILE, wave, lane); };
+  auto load_v = [&](int b) { dma_tile<kKV, 4>(vbase + static_cast<size_t>(b) * TILE, sV + (b & 1) * TILE, wave, lane); };
+
+  load_k(0);
+  load_v(0);
+  if (nblocks > 1) load_k(1);
+  vec qop[8];
+  {
+    const uint16_t* qp = a.q + hoff + static_cast<size_t>(qrow >> 5) * 4096 + (qrow & 31) * 8;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int qi = 8 * (r >> 2) + 4 * hh + (r & 3);
-    const float inv = 1.0f / __shfl(ltot, qi);
-    if (q0 + qi < N) {
-      const size_t obase = (static_cast<size_t>(bh) * N + q0 + qi) * kD + j;
+    for (int kc = 0; kc < 8; ++kc) qop[kc] = as_vec<vec>(*reinterpret_cast<const uint4*>(qp + (kc * 2 + hh) * 256));
+  }
+  v16f of[4];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const float v = of[mt][r] * inv;
-        if (a.out_dtype == 2) static_cast<float*>(a.o)[obase + mt * 32] = v;
-        else static_cast<uint16_t*>(a.o)[obase + mt * 32] = f2h(v, a.out_dtype == 1);
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) of[mt][r] = 0.f;
+  float m = -INFINITY, l = 0.f, gmax = -INFINITY;
+  dma_wait();
+  __syncthreads();
+
+  v16f sa[NCW], sb[NCW];
+  auto scores = [&](const uint16_t* kt, v16f (&s)[NCW]) {
+#pragma unroll
+    for (int c = 0; c < NCW; ++c) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[c][r] = 0.f;
+#pragma unroll
+      for (int kc = 0; kc < 8; ++kc) {
+        const vec op = as_vec<vec>(
+            *reinterpret_cast<const uint4*>(&kt[((((kh * NCW + c) * 8 + kc) * 2 + hh) * 32 + j) * 8]));
+        s[c] = MF<F16>::mfma(op, qop[kc], s[c]);
       }
     }
+  };
+  // the scores of block jn are in s: keys past N masked, the half's row maximum
+  // left for the row's other wave
+  auto finish_scores = [&](int jn, v16f (&s)[NCW]) {
+    if (jn == nblocks - 1 && N % kKV != 0) {
+#pragma unroll
+      for (int c = 0; c < NCW; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (jn * kKV + (kh * NCW + c) * 32 + 8 * (r >> 2) + 4 * hh + (r & 3) >= N) s[c][r] = -INFINITY;
+    }
+    float mx = -3.40282347e38f;   // stays when every key of the half is masked
+#pragma unroll
+    for (int c = 0; c < NCW; ++c) {
+      float cx = -3.40282347e38f;
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) cx = fmaxf(fmaxf(cx, s[c][r]), s[c][r + 1]);
+      mx = fmaxf(mx, cx);
+    }
+    gmax = max_halves(mx > -3.0e38f ? __fmul_rn(mx, Kc) : -INFINITY);
+    if (hh == 0) sM[jn & 1][wave][j] = gmax;
+  };
+  scores(sK, sa);
+  finish_scores(0, sa);
+  __syncthreads();   // the maxima are visible; block 0's K has been read
+
+  auto step = [&](int jb, v16f (&s)[NCW], v16f (&sn)[NCW], auto last_tag) {
+    constexpr bool LAST = decltype(last_tag)::value;
+    if (!LAST) {
+      if (jb + 2 < nblocks) load_k(jb + 2);
+      load_v(jb + 1);
+      scores(sK + ((jb + 1) & 1) * TILE, sn);
+    }
+    const float mnew = fmaxf(m, fmaxf(gmax, sM[jb & 1][wave ^ 2][j]));
+    const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+    m = mnew;
+    if (__any(alpha != 1.0f)) {
+      const RowFactors ab = row_factors(alpha);
+      each16([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        const float ar = row_factor<r>(ab);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) of[mt][r] = __fmul_rn(of[mt][r], ar);
+      });
+    }
+    float ls[4];
+    const uint16_t* vt = sV + (jb & 1) * TILE;
+#pragma unroll
+    for (int c = 0; c < NCW; ++c) {
+      uint32_t pw[8];
+#pragma unroll
+      for (int r2 = 0; r2 < 8; ++r2) {
+        float P[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int r = 2 * r2 + u;
+          float p = __builtin_amdgcn_exp2f(__fmaf_rn(s[c][r], Kc, -mnew));
+          if (LAST && s[c][r] == -INFINITY) p = 0.f;
+          if (c == 0 && r < 4) ls[r] = p;
+          else ls[r & 3] += p;
+          P[u] = p;
+        }
+        pw[r2] = pack2<F16>(P[0], P[1]);
+      }
+#pragma unroll
+      for (int stp = 0; stp < 2; ++stp) {
+        const vec A = as_vec<vec>(make_uint4(pw[4 * stp], pw[4 * stp + 1], pw[4 * stp + 2], pw[4 * stp + 3]));
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+          const vec op = as_vec<vec>(*reinterpret_cast<const uint4*>(
+              &vt[((((kh * NCW + c) * 2 + stp) * 2 + hh) * 128 + mt * 32 + j) * 8]));
+          of[mt] = MF<F16>::mfma(A, op, of[mt]);
+        }
+      }
+    }
+    l = __fmaf_rn(l, alpha, (ls[0] + ls[1]) + (ls[2] + ls[3]));
+    if (!LAST) {
+      finish_scores(jb + 1, sn);
+      dma_wait();
+    }
+    __syncthreads();
+  };
+  using kNo = std::integral_constant<bool, false>;
+  int jb = 0;
+  for (; jb + 2 < nblocks; jb += 2) {
+    step(jb, sa, sb, kNo());
+    step(jb + 1, sb, sa, kNo());
+  }
+  if (jb + 1 < nblocks) {
+    step(jb, sa, sb, kNo());
+#pragma unroll
+    for (int c = 0; c < NCW; ++c) sa[c] = sb[c];
+  }
+  step(nblocks - 1, sa, sb, std::integral_constant<bool, true>());
+
+  // each wave finishes two of the row's four output tiles: it hands the other
+  // two to its partner (the tiles have all been read)
+  float* ox = reinterpret_cast<float*>(sT);
+  float* mine = ox + wave * 32 * 64 + lane;
+  const float* theirs = ox + (wave ^ 2) * 32 * 64 + lane;
+  sL[wave][lane] = l;
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mine[(mt * 16 + r) * 64] = kh == 0 ? of[2 + mt][r] : of[mt][r];
+  __syncthreads();
+  l += sL[wave ^ 2][lane];
+  const float ltot = l + __shfl_xor(l, 32);
+  auto take = [&](int t0) {
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) of[t0 + mt][r] += theirs[(mt * 16 + r) * 64];
+  };
+  if (kh == 0) {
+    take(0);
+    finish_rows<0, 2>(a, of, ltot, bh, q0, hh, j);
+  } else {
+    take(2);
+    finish_rows<2, 2>(a, of, ltot, bh, q0, hh, j);
   }
 }
 
@@ -482,16 +700,29 @@ hipError_t launch_prepare16(const RopeTables& t, const uint32_t* tsrc, uint32_t*
   return hipGetLastError();
 }
 
-hipError_t launch_attn_fp16(const Fp16Args& a, int kv_block, hipStream_t s) {
-  const dim3 grid(a.Npad / kBlockM, a.BH);
-  if (kv_block == 128) {
-    if (a.is_fp16) hipLaunchKernelGGL((k_attn16<true, 128>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_attn16<false, 128>), grid, dim3(256), 0, s, a);
-  } else {
-    if (a.is_fp16) hipLaunchKernelGGL((k_attn16<true, 64>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_attn16<false, 64>), grid, dim3(256), 0, s, a);
-  }
+// Whole rounds of 256-query workgroups, one per compute unit, on the 8-wave
+// kernel; a last round of up to half the units on 128-query workgroups of 4
+// waves (one wave per SIMD), of up to a quarter on the key-split kernel.
+// Measured, kv_block 64, 8 waves / 4 waves / key-split: 7 tiles (1560 tokens, 1
+// head) 49 / 39 / 33 us; 42 tiles 54 / 44 / 38; 84 tiles 58 / 48 / 52; 126 tiles
+// 61 / 51 / 55; 168 tiles 62 / 64 / 82; 320 tiles (20280 tokens, 4 heads) 1043 /
+// 1001 / 862 us.
+template <bool F16, int KV>
+hipError_t launch_attn16(const Fp16Args& a, hipStream_t s) {
+  constexpr int kUnits = 256;   // compute units of the chip
+  const int total = (a.Npad + 255) / 256 * a.BH;
+  int rest = total % kUnits;
+  if (2 * rest > kUnits) rest = 0;
+  const int whole = total - rest;
+  if (whole) hipLaunchKernelGGL((k_attn16<F16, KV, 8>), dim3(whole), dim3(512), 0, s, a, 0);
+  if (4 * rest > kUnits) hipLaunchKernelGGL((k_attn16<F16, KV, 4>), dim3(2 * rest), dim3(256), 0, s, a, whole);
+  else if (rest) hipLaunchKernelGGL((k_attn16_split<F16, KV>), dim3(4 * rest), dim3(256), 0, s, a, whole);
   return hipGetLastError();
+}
+
+hipError_t launch_attn_fp16(const Fp16Args& a, int kv_block, hipStream_t s) {
+  if (kv_block == 128) return a.is_fp16 ? launch_attn16<true, 128>(a, s) : launch_attn16<false, 128>(a, s);
+  return a.is_fp16 ? launch_attn16<true, 64>(a, s) : launch_attn16<false, 64>(a, s);
 }
 
 }  // namespace ra

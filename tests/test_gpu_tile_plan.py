@@ -1,7 +1,7 @@
-"""The 256-query tiles of a FP6 attention call are divided between the plain
-kernel and the key-split one by their number (kv_block 128): a last round of
-at most 128 tiles on 256 compute units runs split.  The small parity cases all
-fall to the split kernel; here the plain kernel runs at the same small sizes
+"""The 256-query tiles of an attention call are divided between kernels by their
+number: whole rounds of 256 tiles (one per compute unit) on the plain kernel, a
+last round of at most 128 tiles in halves or quarters.  The small parity cases
+all fall to the latter; here the plain kernel runs at the same small sizes
 (129 to 256 tiles), both together (257 and more), and the counts on either
 side of the line, with the options that have instantiations of their own.
 Sampled heads, among them those at the border, against the oracle: S and the
@@ -18,13 +18,20 @@ pytestmark = pytest.mark.gpu
 
 # heads, grid, case (rotation, q_group, k_group, v_group, kv_block, P mapping, smoothing, V Hadamard, l from codes)
 PLANS = [
-    (128, (1, 3, 5), (1, 128, 128, 128, 128, 0, 3, 0, 0)),     # 128 tiles: all split
+    (64, (1, 3, 5), (1, 128, 128, 128, 128, 0, 3, 0, 0)),      # 64 tiles: all in quarters
+    (65, (1, 3, 5), (1, 128, 128, 128, 128, 0, 3, 0, 0)),      # 65: all in halves
+    (33, (3, 10, 10), (2, 64, 32, 128, 128, 0, 7, 1, 1)),      # 66 in halves, 300 tokens, key bias
+    (64, (3, 10, 10), (2, 1, 1, 128, 64, 1, 3, 0, 0)),         # 128 in halves, kv_block 64, per-token
+    (128, (1, 3, 5), (1, 1, 1, 128, 128, 0, 3, 0, 0)),         # 128 per-token: quarters
+    (129, (1, 3, 43), (1, 128, 64, 128, 64, 0, 7, 0, 0)),      # 129 plain, kv_block 64, key bias
+    (193, (3, 10, 10), (1, 128, 128, 128, 128, 0, 3, 0, 0)),   # 386: 256 plain, then 130: plain too
+    (165, (3, 10, 10), (1, 128, 128, 128, 128, 0, 3, 0, 0)),   # 330: 256 plain, 74 in halves
     (129, (1, 3, 43), (1, 128, 128, 128, 128, 0, 3, 0, 0)),    # 129: all plain, two blocks, the second of one key
     (65, (3, 10, 10), (1, 1, 1, 128, 128, 0, 7, 0, 0)),        # 130 plain, per-token scales with the key bias
     (130, (1, 8, 16), (2, 128, 32, 256, 128, 1, 3, 0, 1)),     # one full block, SYM7, l from the codes
     (86, (5, 7, 11), (1, 128, 128, 128, 128, 0, 7, 1, 0)),     # 172 plain, four blocks, key bias, V Hadamard
-    (129, (1, 1, 257), (2, 1, 16, 128, 128, 0, 3, 0, 0)),      # 258: 256 plain, 2 split (the last head)
-    (257, (1, 8, 8), (1, 128, 64, 128, 128, 0, 3, 0, 0)),      # 256 plain, 1 split, half a block of keys
+    (129, (1, 1, 257), (2, 1, 16, 128, 128, 0, 3, 0, 0)),      # 258: 256 plain, 2 in quarters (the last head)
+    (257, (1, 8, 8), (1, 128, 64, 128, 128, 0, 3, 0, 0)),      # 256 plain, 1 in quarters, half a block of keys
     (130, (1, 15, 25), (3, 1, 128, 1 << 20, 128, 0, 4, 0, 0)), # 260, V scales per channel, Q smoothing alone
 ]
 
@@ -67,7 +74,7 @@ def test_plain_and_split_tiles(ora, plan):
     _check(ora, w, case, sorted({0, min(127, H - 1), H - 2, H - 1}), *_inputs(w))
 
 
-@pytest.mark.parametrize("heads,kv", [(1, 128), (130, 128), (1, 64)])
+@pytest.mark.parametrize("heads,kv", [(1, 128), (70, 128), (130, 128), (1, 64), (130, 64)])
 def test_wholly_masked_chunk_has_no_maximum(ora, heads, kv):
     """Fewer tokens than one 32-key chunk with K scales per 32 keys: the other
     chunks' groups hold no token and have scale 0.  With every score negative
@@ -86,3 +93,36 @@ def test_wholly_masked_chunk_has_no_maximum(ora, heads, kv):
     _, d = ora.fwd_int4_head(geo, cfg, q[0, 0], k[0, 0], v[0, 0], dumps=True)
     assert d["m"].max() < 0
     _check(ora, w, case, [0, heads - 1], q, k, v)
+
+
+# heads at one tile each (64 tokens) or two (300 tokens): 64, 65, 128 and 129
+# tiles on either side of the lines, then whole rounds with each kind of rest
+@pytest.mark.parametrize("fp16", [False, True])
+@pytest.mark.parametrize("kv", [64, 128])
+@pytest.mark.parametrize("heads,grid", [(64, (1, 8, 8)), (65, (1, 8, 8)), (128, (1, 7, 9)), (129, (1, 8, 8)),
+                                        (257, (1, 8, 8)), (330, (1, 8, 8)), (33, (3, 10, 10)), (65, (3, 10, 10))])
+def test_fallback_tiles(ora, heads, grid, kv, fp16):
+    """The 16-bit fallback on each of its kernels: sampled heads against the
+    fallback oracle, every row written."""
+    from paper_2607_02584_amd import datagen as dg
+    torch, ra = _torch(), _ra()
+    print(f"[fallback tiles] H={heads} grid={grid} kv={kv} fp16={fp16}", flush=True)
+    w = dg.small_workload("fbplan", *grid, H=heads, seed=97)
+    q, k, v = _inputs(w)
+    if fp16:
+        # binary16 products carry 22 bits, so the order of the binary32 sums of
+        # a score shows: up to 128 * 2^-24 of it, and ln 2 times that, on the
+        # log2 scale, in P.  0.2 on Q and K keeps the scaled scores below 200
+        # (they reach 5000 unscaled): at most 1e-3.
+        q, k = (dg.f32_to_bf16_bits(0.2 * dg.bf16_bits_to_f32(x)) for x in (q, k))
+        q, k, v = (np.clip(dg.bf16_bits_to_f32(x), -1000, 1000).astype(np.float16).view(np.uint16) for x in (q, k, v))
+    p = ra.make_params(1, heads, grid, w.split, w.theta, rotation=ra.ROT_NONE, kv_block=kv, out_dtype=ra.FP32,
+                       in_dtype=ra.FP16 if fp16 else ra.BF16)
+    o = torch.full((heads, w.N, 128), float("nan"), dtype=torch.float32, device="cuda")
+    ra.fwd_fp16(p, *(ra.to_device_bits(x) for x in (q, k, v)), o, ra.workspace(p, ra.PATH_FP16))
+    torch.cuda.synchronize()
+    assert torch.isfinite(o).all()
+    geo = _geo(ora, w)
+    for h in sorted({0, min(63, heads - 1), heads - 2, heads - 1}):
+        ref = ora.fwd_fp16_head(geo, q[0, h], k[0, h], v[0, h], kv_block=kv, fp16=fp16)
+        assert np.abs(o[h].cpu().numpy() - ref).max() / np.abs(ref).max() <= O_TOL
