@@ -71,10 +71,9 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 // A workgroup of 8 waves (two per SIMD) covers 256 queries and owns a compute
 // unit: the K/V tiles of a block are fetched once per unit, not once per
-// 128 queries.
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kBlockM = 32 * kWaves;  // queries per workgroup
+// 128 queries (workgroups of 4 waves and the key-split kernel serve a last round
+// that does not fill the chip).
+constexpr int kBlockM = 256;  // queries per tile of the list the launches divide
 
 // The form without block scales: with both scale operands the constant 0 the
 // compiler issues v_mfma_f32_32x32x64_f8f6f4, whose scale is 1, instead of the
@@ -193,10 +192,12 @@ __device__ __forceinline__ v8i load_rec(const uint8_t* p) {
 // end of block j and written to LDS in block j + 1, once its first 64-key
 // group is packed, so their latency overlaps the barrier, the row maxima and
 // the first probabilities.
-template <int KV>
+template <int KV, int NW>
 struct TilePiece {
-  // 8-byte (KV = 128) or 4-byte (KV = 64) pieces as 32-bit vectors, six per thread
-  typedef unsigned T __attribute__((ext_vector_type(KV == 128 ? 2 : 1)));
+  static constexpr int kThreads = 64 * NW;
+  // 8-byte (KV = 128) or 4-byte (KV = 64) pieces as 32-bit vectors, six per
+  // thread; twice that with 4 waves
+  typedef unsigned T __attribute__((ext_vector_type(KV / 64 * (8 / NW))));
   T k0, k1, k2, v0, v1, v2;
   __device__ __forceinline__ void load(const uint8_t* kg, const uint8_t* vg, int tid) {
     const T* K = reinterpret_cast<const T*>(kg) + tid;
@@ -295,8 +296,12 @@ __device__ __forceinline__ void finish_rows(const AttnArgs& a, v16f (&of)[4], fl
 // QB: Q smoothing, every key carries the score bias fl(b_j Kc), the scores
 // become t = fma(S, c, bias) before the maximum and P = 2^(t - m).
 // LQ: the normaliser sums the codes u = rint(pscale P) (l = sum of P^) instead of pscale P.
-template <int KV, bool KTOK, bool SYM7, bool DEBUG, bool QB, bool LQ>
-__global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) {
+// NW: waves per workgroup, 8 (a 256-query tile, one workgroup per compute unit)
+// or 4 (half a tile; for a last round that would leave units idle).  The launch
+// covers the tiles from tile0 of the list (head by head) on.
+template <int KV, bool KTOK, bool SYM7, bool DEBUG, bool QB, bool LQ, int NW>
+__global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_e2m3(AttnArgs a, int tile0) {
+  constexpr int kThreads = 64 * NW;
   constexpr int NCH = KV / 32;   // 32-key chunks
   constexpr int NG = KV / 64;    // 64-key groups (one PV instruction each)
   constexpr int KB = KV * 96;    // bytes of K (and of V) codes per block
@@ -311,12 +316,13 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
   // the wave index is uniform: conditions on it are scalar branches
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hh = lane >> 5, j = lane & 31;
-  // the launch covers the first gridDim.x of the list of 256-query tiles (head
-  // by head); the split kernel covers the others
+  constexpr int PER = 8 / NW;   // workgroups per tile
   const int ntile = (a.Npad + kBlockM - 1) / kBlockM;
-  const int L = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
-  const int bh = L / ntile, qtile = L - bh * ntile;
-  const int qrow = qtile * kBlockM + wave * 32 + j;
+  const int U = PER * tile0 + xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+  const int bh = U / PER / ntile;
+  const int wq0 = (U / PER - bh * ntile) * kBlockM + (U % PER) * (32 * NW);
+  if (wq0 >= a.N) return;   // the last tile of a head may reach past its tokens
+  const int q0 = wq0 + wave * 32, qrow = q0 + j;
   const int N = a.N;
   const int nblocks = (N + KV - 1) / KV;
   const int kstride = a.Npad / a.k_group;
@@ -404,16 +410,16 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
   float m = -INFINITY, l = 0.f;
   int vr = 0;
 
-  static_assert(KB == 3 * kThreads * static_cast<int>(sizeof(typename TilePiece<KV>::T)), "three pieces per thread");
+  static_assert(KB == 3 * kThreads * static_cast<int>(sizeof(typename TilePiece<KV, NW>::T)), "three pieces per thread");
   // Three tile buffers: block j's tiles sit in buffer j % 3; block j + 1's are
   // already in LDS while block j is processed (its score products run during
   // block j's probabilities), and block j + 2's are written during block j.
   const int t1 = nblocks > 1 ? 1 : 0, t2 = nblocks > 2 ? 2 : nblocks - 1;
   // All requests of the prologue go out before the first is waited for.
-  TilePiece<KV> tp;
+  TilePiece<KV, NW> tp;
   Aux pf{0.f, 0.f, 0.f};
   {
-    TilePiece<KV> tp0;
+    TilePiece<KV, NW> tp0;
     tp0.load(kbase, vbase, tid);
     tp.load(kbase + t1 * KB, vbase + t1 * KB, tid);
     const Aux f0 = fetch_aux(0);
@@ -789,7 +795,7 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void k_attn_e2m3(AttnArgs a) 
   if (tid < kD) sW[tid] = wcur;
   __syncthreads();
 
-  finish_rows(a, of, l, sW, bh, qtile * kBlockM + wave * 32, hh, j);
+  finish_rows(a, of, l, sW, bh, q0, hh, j);
 }
 
 // ------------------------------------------------ key-split variant (KV = 128) --
@@ -1164,35 +1170,34 @@ __global__ __launch_bounds__(kSplitThreads, DEBUG ? 1 : 2) void k_attn_e2m3_spli
   finish_rows(a, of, l + sL[qs][lane], sW, bh, q0, hh, j);
 }
 
-// Which of the 256-query tiles run on the plain kernel and which on the
-// key-split one (KV = 128).  A round is one plain workgroup on every compute
-// unit; a last round of at most half the units leaves the others idle, and its
-// tiles, split in four, run two workgroups to a unit (one wave of each per
-// SIMD) in less than a plain round: 0.69 of it at up to a quarter of the units,
-// 0.85 at half (measured, both ways, at 7800 tokens: 2 heads 150 -> 111 us, 4
-// heads 154 -> 135 us; 32760 tokens and 3 heads 1013 -> 942 us; 1024 tokens and
-// 2 heads 43 -> 37 us).  Above half the split tiles take two rounds and lose:
-// 7800 tokens and 6 heads 161 -> 224 us, 1024 tokens and 40 heads 53 -> 64 us.
-struct TilePlan {
-  int plain, split;   // tiles of the linear list: the first `plain`, then `split`
-};
-inline TilePlan plan_tiles(int total) {
-  constexpr int kUnits = 256;   // compute units of the chip
-  const int rest = total % kUnits;
-  if (2 * rest > kUnits) return {total, 0};
-  return {total - rest, rest};
-}
-
+// Whole rounds of 256-query tiles, one workgroup per compute unit, run on the
+// 8-wave kernel.  A last round of at most half the units would leave the others
+// idle: its tiles run in smaller workgroups, in four on the key-split kernel (KV
+// = 128) while that is at most one workgroup a unit, in two of 4 waves above
+// that (one wave per SIMD).  Measured, 8 waves / halves / quarters (the whole
+// forward): 8 tiles (1024 tokens, 2 heads) 43 / 39.6 / 35.9 us; 62 tiles (7800
+// tokens) 150 / 126 / 109; 124 tiles 154 / 130 / 134; 128 tiles after a whole
+// round (32760 tokens, 3 heads) 1013 / 926 / 936; with Q smoothing 1152 / 1072 /
+// 1117; with per-token K scales 1344 / 1235 / 1223, so those stay on quarters.
+// Above half the units both lose (186 tiles 161 / - / 224 us).
 template <int KV, bool KTOK, bool SYM7, bool DEBUG, bool QB, bool LQ>
 hipError_t launch_l(const AttnArgs& a, hipStream_t s) {
+  constexpr int kUnits = 256;   // compute units of the chip
+  constexpr int kSplitMax = KV != 128 ? 0 : (KTOK ? kUnits / 2 : kUnits / 4);
   const int total = (a.Npad + kBlockM - 1) / kBlockM * a.BH;
-  TilePlan p{total, 0};
-  if (KV == 128) p = plan_tiles(total);
-  if (p.plain) hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ>), dim3(p.plain), dim3(kThreads), 0, s, a);
-  if constexpr (KV == 128) {
-    if (p.split)
-      hipLaunchKernelGGL((k_attn_e2m3_split<KTOK, SYM7, DEBUG, QB, LQ>), dim3(4 * p.split), dim3(kSplitThreads), 0, s, a,
-                         p.plain);
+  int rest = total % kUnits;
+  if (rest > kUnits / 2) rest = 0;
+  const int whole = total - rest;
+  if (whole)
+    hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ, 8>), dim3(whole), dim3(512), 0, s, a, 0);
+  if constexpr (kSplitMax > 0) {
+    if (rest && rest <= kSplitMax)
+      hipLaunchKernelGGL((k_attn_e2m3_split<KTOK, SYM7, DEBUG, QB, LQ>), dim3(4 * rest), dim3(kSplitThreads), 0, s, a,
+                         whole);
+  }
+  if constexpr (kSplitMax < kUnits / 2) {
+    if (rest > kSplitMax)
+      hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ, 4>), dim3(2 * rest), dim3(256), 0, s, a, whole);
   }
   return hipGetLastError();
 }
