@@ -26,7 +26,8 @@
 // t/4 + 64p (p = 0, 1), each row read as four 64-byte pieces, with the RoPE
 // table rows the tile needs staged in LDS.  V: thread t handles channels
 // 4*(t%32) .. +3 of the rows t/32 + 8p (16 rows), each row read as 32 8-byte
-// pieces.  A pass is bound by its HBM traffic and by the per-element vector
+// pieces; for the codes of the E2M3 container a wave holds 32 tokens of every
+// channel (v_quant_e2m3).  A pass is bound by its HBM traffic and by the per-element vector
 // work (RoPE, rotation, quantization, packing) together: the jobs of one
 // pass share one grid, one job after another in the grid's order (one launch,
 // and the end of one job overlaps the start of the next; taking the jobs in
@@ -686,6 +687,119 @@ __device__ __forceinline__ void v_amax_body(const VArgs& a, int tile, int bh, ui
   }
 }
 
+// LDS of v_quant_e2m3: the partial maxima of the four waves.
+constexpr int kVQuantE2m3LdsBytes = 4 * kD * 4;
+
+// V codes in the E2M3 container, one workgroup per (tile, head).  Record
+// ((gl*4 + ch/32)*2 + h)*32 + ch%32 holds the 32 tokens kappa of group gl of 64
+// with (kappa/4)%2 = h, token kappa in field 8*((kappa%32)/8) + 2*(kappa%4) +
+// kappa/32.  Wave (gl, h) holds all 32 tokens of channels 2 lane, 2 lane + 1:
+// a token row is one 256-byte load of the wave, the two records are packed by
+// one FP6 conversion each and leave from registers as 48 contiguous bytes, and
+// only the maxima cross waves.  (Threads of 4 channels x 16 tokens hold a piece
+// of every record: merging the pieces by LDS atomics took about fourteen
+// vector instructions per code, 48 atomics per thread and three more barriers.)
+// Bound by the round of loads, arithmetic and stores of few tiles per unit.
+// 32760 tokens, 12 heads, all producers: 163.4 -> 155.4 us (2.7 TB/s of the
+// 417 MB that a call reads and writes once).
+template <bool F16>
+__device__ __forceinline__ void v_quant_e2m3(const VArgs& a, int tile, int bh, uint8_t* lds) {
+  float (*red)[kD] = reinterpret_cast<float (*)[kD]>(lds);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int gl = wave >> 1, h = wave & 1, ch = 2 * lane;
+  const int N = a.N, n0 = tile * kTile + gl * 64;
+  // register i holds token 8 (i / 4) + 4 h + i % 4 of the group (rows past N
+  // re-read the last row; their codes are replaced below)
+  auto token = [&](int i) { return n0 + 8 * (i >> 2) + 4 * h + (i & 3); };
+  const bool tail = n0 + 64 > N;
+  const int first = n0 < N ? n0 : N - 1;
+  const uint16_t* xb = a.x + (static_cast<size_t>(bh) * N + first) * kD + ch;
+  uint32_t raw[32];
+  if (!tail) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) raw[i] = *reinterpret_cast<const uint32_t*>(xb + (token(i) - n0) * kD);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      const int n = token(i) < N ? token(i) : N - 1;
+      raw[i] = *reinterpret_cast<const uint32_t*>(xb + (n - first) * kD);
+    }
+  }
+  float mu[2] = {0.f, 0.f};   // not centred: x - 0 == x exactly, also for -0
+  if (a.center) {
+    const double den = static_cast<double>(N) * 1048576.0;
+    const double* sums = a.sums + static_cast<size_t>(bh) * kD;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) mu[c] = static_cast<float>(sums[ch + c] / den);
+    if (a.mu_out && tile == 0 && wave == 0) {
+      a.mu_out[bh * kD + ch] = mu[0];
+      a.mu_out[bh * kD + ch + 1] = mu[1];
+    }
+  }
+  // the centred value of register i, channel ch + c
+  auto centred = [&](int i, int c) {
+    return __fsub_rn(h2f<F16>(static_cast<uint16_t>(c ? raw[i] >> 16 : raw[i] & 0xffff)), mu[c]);
+  };
+  const int g = vgroup_of(a, first);
+  float m[2] = {0.f, 0.f};
+  if (a.local_amax) {
+    // groups of 64 or 128 tokens lie inside this tile
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 32; ++i) m[c] = fmaxf(m[c], fabsf(centred(i, c)));
+    // (a group with no token has no maximum; a repeated row is of the same group)
+    if (n0 >= N) m[0] = m[1] = 0.f;
+    *reinterpret_cast<float2*>(&red[wave][ch]) = make_float2(m[0], m[1]);
+    __syncthreads();
+    const bool whole = a.group != 64;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (whole || (w >> 1) == gl) {
+        const float2 o = *reinterpret_cast<const float2*>(&red[w][ch]);
+        m[0] = fmaxf(m[0], o.x);
+        m[1] = fmaxf(m[1], o.y);
+      }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) m[c] = __uint_as_float(a.amax[(static_cast<size_t>(bh) * a.ngroups + g) * kD + ch + c]);
+  }
+  // the tile half holding the first token of group g writes its scales
+  const bool writes = h == 0 && n0 < N && g * a.group >= n0 && g * a.group < n0 + 64;
+  uint32_t w[12];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    float s = 0.f, inv = 0.f;
+    if (m[c] > 0.f) {
+      s = __fdiv_rn(m[c], 7.0f);
+      inv = __fdiv_rn(7.0f, m[c]);
+    }
+    if (writes) a.scales[(static_cast<size_t>(bh) * a.ngroups + g) * kD + ch + c] = s;
+    v16f_ ev, od;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      ev[i] = qcode_f(centred(i, c), inv);
+      od[i] = qcode_f(centred(16 + i, c), inv);
+    }
+    if (tail) {
+      const float none = qcode_f(0.f, inv);   // rows past N are zero
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (token(i) >= N) ev[i] = none;
+        if (token(16 + i) >= N) od[i] = none;
+      }
+    }
+    const v6i_ f = pack_e2m3(ev, od);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) w[6 * c + i] = static_cast<uint32_t>(f[i]);
+  }
+  const int rec = ((gl * 4 + (ch >> 5)) * 2 + h) * 32 + (ch & 31);
+  uint4* d = reinterpret_cast<uint4*>(a.codes + static_cast<size_t>(bh) * a.Npad * 96 +
+                                      static_cast<size_t>(tile) * kTile * 96 + rec * 24);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) d[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+}
+
 // LDS: the tile's codes (12 KB), 2 x 128 inverse scales, 8 x 2 x 128 floats.
 constexpr int kVQuantLdsBytes = kTile * 96 + 2 * kD * 4 + 8 * 2 * kD * 4;
 
@@ -828,7 +942,17 @@ __global__ __launch_bounds__(256) void k_pass(RopeTables t, PassArgs pa) {
     case kQkQuant: qk_body<ROT, F16, STAGED, false>(t, qa, tile, bh, lds); break;
     case kVSums: v_sums_body<F16, VHAD>(va, tile, bh, lds); break;
     case kVAmax: v_amax_body<F16, VHAD>(va, tile, bh, lds); break;
-    case kVQuant: v_quant_body<F16, VHAD>(va, tile, bh, lds); break;
+    case kVQuant:
+      // the online V rotation pairs the channels of a row across its lanes,
+      // in v_quant_body's layout
+      if constexpr (!VHAD) {
+        if (va.e2m3) {
+          v_quant_e2m3<F16>(va, tile, bh, lds);
+          break;
+        }
+      }
+      v_quant_body<F16, VHAD>(va, tile, bh, lds);
+      break;
     default: break;
   }
 }
@@ -861,13 +985,13 @@ __global__ __launch_bounds__(256) void k_write_floats(FloatChunk c, float* dst) 
 namespace {
 
 // LDS bytes one job of a pass needs (stage: the staged table rows, or 0).
-size_t job_lds(int kind, size_t stage) {
-  switch (kind) {
+size_t job_lds(const PassJob& job, size_t stage) {
+  switch (job.kind) {
     case kQkSums: return kQkSmallBytes + (stage > kSumLdsBytes ? stage : kSumLdsBytes);
     case kQkQuant: return kQkSmallBytes + stage;
     case kVSums: return 8 * kD * sizeof(double);
     case kVAmax: return 8 * 2 * kD * sizeof(float);
-    case kVQuant: return kVQuantLdsBytes;
+    case kVQuant: return job.v.e2m3 && !job.v.vhad ? kVQuantE2m3LdsBytes : kVQuantLdsBytes;
     default: return 0;
   }
 }
@@ -898,7 +1022,7 @@ hipError_t launch_pass(const RopeTables& t, const PassArgs& pa, hipStream_t s) {
   size_t lds = 0;
   bool f16 = false, vhad = false;
   for (int j = 0; j < pa.njobs; ++j) {
-    const size_t need = job_lds(pa.job[j].kind, stage);
+    const size_t need = job_lds(pa.job[j], stage);
     if (need > lds) lds = need;
     const int k = pa.job[j].kind;
     if (k == kQkSums || k == kQkQuant) f16 = pa.job[j].qk.is_fp16 != 0;
