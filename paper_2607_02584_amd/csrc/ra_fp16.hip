@@ -569,7 +569,10 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16_split(Fp16Arg
         for (int r = 0; r < 16; ++r)
           if (jn * kKV + (kh * NCW + c) * 32 + 8 * (r >> 2) + 4 * hh + (r & 3) >= N) s[c][r] = -INFINITY;
     }
-    float mx = -3.40282347e38f;   // stays when every key of the half is masked
+    // (seeded as in the plain kernel: the seed stays for a half whose scores are
+    // all -inf, masked or not, and is below every other score of the row; -inf in
+    // its place would make alpha of a first block without a finite score 2^NaN)
+    float mx = -3.40282347e38f;
 #pragma unroll
     for (int c = 0; c < NCW; ++c) {
       float cx = -3.40282347e38f;
@@ -577,7 +580,7 @@ __global__ __launch_bounds__(256, kKV == 64 ? 2 : 1) void k_attn16_split(Fp16Arg
       for (int r = 0; r < 16; r += 2) cx = fmaxf(fmaxf(cx, s[c][r]), s[c][r + 1]);
       mx = fmaxf(mx, cx);
     }
-    gmax = max_halves(mx > -3.0e38f ? __fmul_rn(mx, Kc) : -INFINITY);
+    gmax = max_halves(__fmul_rn(mx, Kc));
     if (hh == 0) sM[jn & 1][wave][j] = gmax;
   };
   scores(sK, sa);

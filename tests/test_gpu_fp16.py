@@ -131,3 +131,34 @@ def test_fallback_c2_full_size_sampled_rows(ora):
             err = np.abs(og - O_ref).max() / np.abs(O_ref).max()
             print(f"  head {hh} rows {r0}+{nr}: O rel err {err:.3e}", flush=True)
             assert err <= O_TOL
+
+
+# 2 heads of one 256-query tile: the key-split kernel; 70: 4 waves; 130 heads of
+# two tiles: a whole round on 8 waves and the last two heads on the key-split kernel
+@pytest.mark.parametrize("heads,n", [(2, 200), (70, 200), (130, 300)])
+@pytest.mark.parametrize("kv", [64, 128])
+def test_fallback_first_block_without_a_finite_score(heads, n, kv):
+    """Every key of the first block (and five of the second) scores -inf: the
+    probabilities of these keys are zero, and the output is the attention over
+    the other keys, on every kernel.  Q and K are zero in the channels that the
+    positions turn (the first two axes have extent 1), so the reference needs
+    no RoPE."""
+    torch, ra = _torch(), _ra()
+    print(f"[fallback -inf] H={heads} N={n} kv={kv}", flush=True)
+    g = torch.Generator().manual_seed(11)
+    q, k, v = (torch.randn((heads, n, 128), generator=g) for _ in range(3))
+    m = kv + 5
+    for x in (q, k):
+        x[..., 86:] = 0
+        x[..., :2] = 0
+    q[..., 0], k[:, :m, 0] = 2.0 ** 70, -2.0 ** 70
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    p = ra.make_params(1, heads, (1, 1, n), rotation=ra.ROT_NONE, kv_block=kv, out_dtype=ra.FP32)
+    o = torch.empty((heads, n, 128), dtype=torch.float32, device="cuda")
+    ra.fwd_fp16(p, q.cuda(), k.cuda(), v.cuda(), o, ra.workspace(p, ra.PATH_FP16))
+    got = o.cpu().double()
+    s = torch.matmul(q[..., 2:].double(), k[:, m:, 2:].double().transpose(1, 2)) / 128 ** 0.5
+    P = torch.softmax(s, 2)
+    ref, mass = torch.matmul(P, v[:, m:].double()), torch.matmul(P, v[:, m:].double().abs())
+    # P is rounded to bfloat16 (relative 2^-9), the sums are binary32: twice that covers both
+    assert ((got - ref).abs() <= 2.0 ** -8 * mass).all()
