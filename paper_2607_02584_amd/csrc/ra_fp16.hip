@@ -20,6 +20,7 @@
 #include <utility>
 
 #include "ra_internal.h"
+#include "ra_plan.h"
 #include "ra_xcd.h"
 
 namespace ra {
@@ -289,10 +290,10 @@ __device__ __forceinline__ void finish_rows(const Fp16Args& a, const v16f (&of)[
 // LDS, and 4 waves were alone with it (32760 tokens 7.40 -> 5.88 ms); at
 // kv_block 64 the unit's tile traffic halves (6.17 -> 5.95 ms; the kernel runs at
 // the power limit there, 1.9 GHz).  4 (128 queries) are for a last round that
-// would leave units idle.  The launch covers the query tiles from the 256-query
-// tile tile0 of the list (head by head) on.
+// would leave units idle, and for heads that 256-query tiles fit badly.  The launch
+// covers a list of tiles of 32 NW queries, per_head of them a head, from tile u0 on.
 template <bool F16, int kKV, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : (kKV == 64 ? 2 : 1)) void k_attn16(Fp16Args a, int tile0) {
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : (kKV == 64 ? 2 : 1)) void k_attn16(Fp16Args a, int u0, int per_head) {
   typedef typename MF<F16>::vec vec;
   constexpr int NCH = kKV / 32;
   constexpr int TILE = kKV * kD;  // elements of K (and of V) per block
@@ -300,11 +301,9 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 1 : (kKV == 64 ? 2 : 1)) void k_
   __shared__ __align__(16) uint16_t sV[2][TILE];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hh = lane >> 5, j = lane & 31;
-  constexpr int PER = 8 / NW;   // workgroups per 256-query tile
-  const int ntile = (a.Npad + 255) / 256;
-  const int U = PER * tile0 + xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
-  const int bh = U / PER / ntile;
-  const int wq0 = (U / PER - bh * ntile) * 256 + (U % PER) * (32 * NW);
+  const int U = u0 + xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+  const int bh = U / per_head;
+  const int wq0 = (U - bh * per_head) * (32 * NW);
   if (wq0 >= a.N) return;   // the last tile of a head may reach past its tokens
   const int q0 = wq0 + wave * 32;
   const int qrow = q0 + j;
@@ -703,23 +702,18 @@ hipError_t launch_prepare16(const RopeTables& t, const uint32_t* tsrc, uint32_t*
   return hipGetLastError();
 }
 
-// Whole rounds of 256-query workgroups, one per compute unit, on the 8-wave
-// kernel; a last round of up to half the units on 128-query workgroups of 4
-// waves (one wave per SIMD), of up to a quarter on the key-split kernel.
-// Measured, kv_block 64, 8 waves / 4 waves / key-split: 7 tiles (1560 tokens, 1
-// head) 49 / 39 / 33 us; 42 tiles 54 / 44 / 38; 84 tiles 58 / 48 / 52; 126 tiles
-// 61 / 51 / 55; 168 tiles 62 / 64 / 82; 320 tiles (20280 tokens, 4 heads) 1043 /
-// 1001 / 862 us.
 template <bool F16, int KV>
 hipError_t launch_attn16(const Fp16Args& a, hipStream_t s) {
   constexpr int kUnits = 256;   // compute units of the chip
-  const int total = (a.Npad + 255) / 256 * a.BH;
-  int rest = total % kUnits;
-  if (2 * rest > kUnits) rest = 0;
-  const int whole = total - rest;
-  if (whole) hipLaunchKernelGGL((k_attn16<F16, KV, 8>), dim3(whole), dim3(512), 0, s, a, 0);
-  if (4 * rest > kUnits) hipLaunchKernelGGL((k_attn16<F16, KV, 4>), dim3(2 * rest), dim3(256), 0, s, a, whole);
-  else if (rest) hipLaunchKernelGGL((k_attn16_split<F16, KV>), dim3(4 * rest), dim3(256), 0, s, a, whole);
+  const TilePlan p = plan_fallback(a.Npad, a.BH, KV, kUnits);
+  const int n256 = (a.Npad + 255) / 256;   // 256-query tiles of a head
+  if (p.tiles128)
+    hipLaunchKernelGGL((k_attn16<F16, KV, 4>), dim3(p.tiles128), dim3(256), 0, s, a, 0, a.Npad / 128);
+  if (p.whole) hipLaunchKernelGGL((k_attn16<F16, KV, 8>), dim3(p.whole), dim3(512), 0, s, a, 0, n256);
+  if (p.halves)
+    hipLaunchKernelGGL((k_attn16<F16, KV, 4>), dim3(2 * p.halves), dim3(256), 0, s, a, 2 * p.whole, 2 * n256);
+  if (p.quarters)
+    hipLaunchKernelGGL((k_attn16_split<F16, KV>), dim3(4 * p.quarters), dim3(256), 0, s, a, p.whole);
   return hipGetLastError();
 }
 
