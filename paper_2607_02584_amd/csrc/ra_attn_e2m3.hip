@@ -56,6 +56,7 @@
 #include <type_traits>
 
 #include "ra_internal.h"
+#include "ra_plan.h"
 #include "ra_xcd.h"
 
 #ifndef RA_E2M3_DEBUG_TU
@@ -1170,34 +1171,20 @@ __global__ __launch_bounds__(kSplitThreads, DEBUG ? 1 : 2) void k_attn_e2m3_spli
   finish_rows(a, of, l + sL[qs][lane], sW, bh, q0, hh, j);
 }
 
-// Whole rounds of 256-query tiles, one workgroup per compute unit, run on the
-// 8-wave kernel.  A last round of at most half the units would leave the others
-// idle: its tiles run in smaller workgroups, in four on the key-split kernel (KV
-// = 128) while that is at most one workgroup a unit, in two of 4 waves above
-// that (one wave per SIMD).  Measured, 8 waves / halves / quarters (the whole
-// forward): 8 tiles (1024 tokens, 2 heads) 43 / 39.6 / 35.9 us; 62 tiles (7800
-// tokens) 150 / 126 / 109; 124 tiles 154 / 130 / 134; 128 tiles after a whole
-// round (32760 tokens, 3 heads) 1013 / 926 / 936; with Q smoothing 1152 / 1072 /
-// 1117; with per-token K scales 1344 / 1235 / 1223, so those stay on quarters.
-// Above half the units both lose (186 tiles 161 / - / 224 us).
 template <int KV, bool KTOK, bool SYM7, bool DEBUG, bool QB, bool LQ>
 hipError_t launch_l(const AttnArgs& a, hipStream_t s) {
-  constexpr int kUnits = 256;   // compute units of the chip
-  constexpr int kSplitMax = KV != 128 ? 0 : (KTOK ? kUnits / 2 : kUnits / 4);
-  const int total = (a.Npad + kBlockM - 1) / kBlockM * a.BH;
-  int rest = total % kUnits;
-  if (rest > kUnits / 2) rest = 0;
-  const int whole = total - rest;
-  if (whole)
-    hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ, 8>), dim3(whole), dim3(512), 0, s, a, 0);
-  if constexpr (kSplitMax > 0) {
-    if (rest && rest <= kSplitMax)
-      hipLaunchKernelGGL((k_attn_e2m3_split<KTOK, SYM7, DEBUG, QB, LQ>), dim3(4 * rest), dim3(kSplitThreads), 0, s, a,
-                         whole);
+  const TilePlan p = plan_e2m3(a.Npad, a.BH, KV, KTOK, a.units);
+  if (p.whole)
+    hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ, 8>), dim3(p.whole), dim3(512), 0, s, a, 0);
+  if constexpr (KV == 128) {
+    if (p.quarters)
+      hipLaunchKernelGGL((k_attn_e2m3_split<KTOK, SYM7, DEBUG, QB, LQ>), dim3(4 * p.quarters), dim3(kSplitThreads), 0,
+                         s, a, p.whole);
   }
-  if constexpr (kSplitMax < kUnits / 2) {
-    if (rest > kSplitMax)
-      hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ, 4>), dim3(2 * rest), dim3(256), 0, s, a, whole);
+  if constexpr (KV != 128 || !KTOK) {   // (per-token scales at 128 have quarters alone)
+    if (p.halves)
+      hipLaunchKernelGGL((k_attn_e2m3<KV, KTOK, SYM7, DEBUG, QB, LQ, 4>), dim3(2 * p.halves), dim3(256), 0, s, a,
+                         p.whole);
   }
   return hipGetLastError();
 }

@@ -704,8 +704,7 @@ hipError_t launch_prepare16(const RopeTables& t, const uint32_t* tsrc, uint32_t*
 
 template <bool F16, int KV>
 hipError_t launch_attn16(const Fp16Args& a, hipStream_t s) {
-  constexpr int kUnits = 256;   // compute units of the chip
-  const TilePlan p = plan_fallback(a.Npad, a.BH, KV, kUnits);
+  const TilePlan p = plan_fallback(a.Npad, a.BH, KV, a.units);
   const int n256 = (a.Npad + 255) / 256;   // 256-query tiles of a head
   if (p.tiles128)
     hipLaunchKernelGGL((k_attn16<F16, KV, 4>), dim3(p.tiles128), dim3(256), 0, s, a, 0, a.Npad / 128);

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <array>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -484,6 +485,21 @@ int produce(const ra_params* p, const ra::RopeTables& t, const TableCopy& tc, co
   return RA_OK;
 }
 
+// Compute units of the current device (a partition of a chip has fewer than the
+// whole one), asked for once per device: they do not change while it is in use.
+int compute_units(int* units) {
+  static std::atomic<int> known[64];
+  int dev = 0;
+  RA_CHECK_HIP(hipGetDevice(&dev));
+  const bool keep = dev >= 0 && dev < 64;
+  *units = keep ? known[dev].load(std::memory_order_relaxed) : 0;
+  if (*units > 0) return RA_OK;
+  RA_CHECK_HIP(hipDeviceGetAttribute(units, hipDeviceAttributeMultiprocessorCount, dev));
+  if (*units <= 0) return fail(RA_ERR_HIP, "the device reports no compute units");
+  if (keep) known[dev].store(*units, std::memory_order_relaxed);
+  return RA_OK;
+}
+
 int attn_impl(const ra_params* p, const uint8_t* qc, const float* qs, const uint8_t* kc, const float* ks,
               const uint8_t* vc, const float* vs, const float* mu_v, const float* kbias, void* o, bool debug, int bh,
               int row0, int rows, int32_t* s_out, uint8_t* u_out, float* m_out, hipStream_t s) {
@@ -517,6 +533,8 @@ int attn_impl(const ra_params* p, const uint8_t* qc, const float* qs, const uint
   a.dbg_row0 = row0;
   a.dbg_rows = rows;
   a.lq = p->l_quant;
+  const int rc = compute_units(&a.units);
+  if (rc) return rc;
   if (p->code_format == RA_CODES_E2M3)
     RA_CHECK_HIP(ra::launch_attn_e2m3(a, p->kv_block, p->k_group < 32, p->p_quant == RA_PQ_SYM7, debug, s));
   else
@@ -552,6 +570,8 @@ int fp16_attn_impl(const ra_params* p, const Fp16Ws& w, void* o, hipStream_t s) 
   a.Kc = kc_of(p);
   a.is_fp16 = p->in_dtype == RA_FP16;
   a.out_dtype = p->out_dtype;
+  const int rc = compute_units(&a.units);
+  if (rc) return rc;
   RA_CHECK_HIP(ra::launch_attn_fp16(a, p->kv_block, s));
   return RA_OK;
 }

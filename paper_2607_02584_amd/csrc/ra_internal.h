@@ -106,6 +106,7 @@ struct AttnArgs {
   int out_dtype;
   int vhad;               // V was rotated by H: rotate each output row back
   int lq;                 // l from the quantized P (sum of the codes) instead of the exact P
+  int units;              // compute units of the device
   // debug dump (debug kernel only)
   int32_t* dbg_s;
   uint8_t* dbg_u;
@@ -121,6 +122,7 @@ struct Fp16Args {
   int N, Npad, BH;
   float Kc;
   int is_fp16, out_dtype;
+  int units;              // compute units of the device
 };
 
 // Producer passes launched together in one grid: job j of a pass covers every

@@ -17,6 +17,9 @@ def plan(tmp_path_factory):
     src.write_text('#include "ra_plan.h"\n'
                    'extern "C" void fallback(int npad, int bh, int kv, int units, int* o) {\n'
                    '  const ra::TilePlan p = ra::plan_fallback(npad, bh, kv, units);\n'
+                   '  o[0] = p.whole, o[1] = p.halves, o[2] = p.quarters, o[3] = p.tiles128;\n}\n'
+                   'extern "C" void e2m3(int npad, int bh, int kv, int ktok, int units, int* o) {\n'
+                   '  const ra::TilePlan p = ra::plan_e2m3(npad, bh, kv, ktok, units);\n'
                    '  o[0] = p.whole, o[1] = p.halves, o[2] = p.quarters, o[3] = p.tiles128;\n}\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
     lib = ctypes.CDLL(str(so))
@@ -28,9 +31,13 @@ def plan(tmp_path_factory):
     return call
 
 
+# a whole chip, partitions of it, and a number that the fractions do not divide
+UNITS = [256, 128, 64, 32, 38]
+
+
+@pytest.mark.parametrize("units", UNITS)
 @pytest.mark.parametrize("kv", [64, 128])
-def test_fallback_plan(plan, kv):
-    units = 256
+def test_fallback_plan(plan, kv, units):
     for n128 in (1, 2, 3, 4, 5, 7, 9, 12, 13, 33, 256):
         for bh in list(range(1, 600)) + [640, 1000, 4096]:
             whole, halves, quarters, tiles128 = plan("fallback", 128 * n128, bh, kv, units)
@@ -44,3 +51,18 @@ def test_fallback_plan(plan, kv):
             rounds = -(-whole // units) + (halves + quarters > 0) + -(-tiles128 // (2 * units))
             if kv == 64:
                 assert rounds <= -(-(n128 * bh) // (2 * units)), (n128, bh)
+
+
+@pytest.mark.parametrize("units", UNITS)
+@pytest.mark.parametrize("kv,ktok", [(64, 0), (64, 1), (128, 0), (128, 1)])
+def test_e2m3_plan(plan, kv, ktok, units):
+    """Whole rounds on the 8-wave kernel, and a last round of at most half the
+    units in smaller workgroups, one a unit (quarters of per-token scales: two)."""
+    for total in range(1, 4 * units):
+        whole, halves, quarters, tiles128 = plan("e2m3", 256, total, kv, ktok, units)
+        assert whole + halves + quarters == total and not tiles128 and not (halves and quarters)
+        rest = total % units
+        assert halves + quarters == (rest if 2 * rest <= units else 0)
+        assert 2 * halves <= units and 4 * quarters <= (2 if ktok else 1) * units
+        assert not quarters or kv == 128
+        assert not halves or kv == 64 or not ktok     # the kernels that are built
