@@ -39,6 +39,12 @@
  *    is ordered with the kernels around it at no extra latency).  Only that
  *    first call per geometry performs a host allocation.
  *  - Results are deterministic: repeated calls give identical bytes.
+ *  - Codes, scales, means and key biases of a head depend on that head's inputs
+ *    alone.  The attention output of a head may differ in its last bits between
+ *    calls of different B * H (a shard of the heads, say): how the binary32 sums
+ *    of a row are divided among waves follows from its tile's place in the
+ *    call and from the device's number of compute units.  The scores, running
+ *    maxima and probabilities are the same bits.
  *
  * Packed INT4 layouts (written by the quantize calls, read by the attention)
  * ------------------------------------------------------------------------

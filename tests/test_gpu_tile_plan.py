@@ -144,3 +144,30 @@ def test_fallback_tiles_of_several_blocks(ora, heads, grid, kv):
     RoPE and the oracle's round some elements next to a tie to different
     neighbours, and one of K in these inputs, 11.43 +- 2^-7, moves O by 2.1e-3.)"""
     _check_fallback(ora, heads, grid, kv, False)
+
+
+@pytest.mark.parametrize("fallback", [False, True])
+def test_a_head_of_another_call(fallback):
+    """The first head of 130 runs on the plain kernel, alone it runs on the
+    key-split one: repeated calls give the same bytes, and the two calls differ by
+    no more than the order of their binary32 sums allows."""
+    torch, ra = _torch(), _ra()
+    print(f"[head of another call] fallback={fallback}", flush=True)
+    N, g = 300, torch.Generator().manual_seed(5)
+    x = [torch.randn((1, 130, N, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(3)]
+
+    def run(H):
+        p = ra.make_params(1, H, (3, 10, 10), rotation=ra.ROT_NONE if fallback else ra.ROT_INTERLEAVED,
+                           out_dtype=ra.FP32)
+        o = torch.empty((H, N, 128), dtype=torch.float32, device="cuda")
+        ra.fwd(p, fallback, *(t[:, :H].contiguous() for t in x), o,
+               ra.workspace(p, ra.PATH_FP16 if fallback else ra.PATH_INT4))
+        torch.cuda.synchronize()
+        return o
+    whole, alone = run(130), run(1)
+    assert torch.equal(whole, run(130)) and torch.equal(alone, run(1))
+    # numerator and l are binary32 sums of N terms and three roundings a block, of
+    # terms whose magnitudes add up to at most max |V| l (4 times that with P codes,
+    # at most 2 P, and centred V, at most 2 max |V|), in two orders each
+    mass = x[2][0, 0].float().abs().max().item() * (1 if fallback else 4)
+    assert (whole[0] - alone[0]).abs().max().item() <= 4 * (N + 3 * 3) * 2.0 ** -24 * mass
