@@ -813,31 +813,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void k_attn_e2m3(AttnArgs a, int t
 constexpr int kSplitThreads = 256;
 constexpr int kSplitM = 64;   // queries per workgroup
 
-struct SplitPiece {
-  // three 16-byte pieces of K and of V per thread cover a 128-key tile
-  typedef unsigned T __attribute__((ext_vector_type(4)));
-  T k0, k1, k2, v0, v1, v2;
-  __device__ __forceinline__ void load(const uint8_t* kg, const uint8_t* vg, int tid) {
-    const T* K = reinterpret_cast<const T*>(kg) + tid;
-    const T* V = reinterpret_cast<const T*>(vg) + tid;
-    k0 = K[0];
-    v0 = V[0];
-    k1 = K[kSplitThreads];
-    v1 = V[kSplitThreads];
-    k2 = K[2 * kSplitThreads];
-    v2 = V[2 * kSplitThreads];
-  }
-  __device__ __forceinline__ void store(uint8_t* ks, uint8_t* vs, int tid) const {
-    T* K = reinterpret_cast<T*>(ks) + tid;
-    T* V = reinterpret_cast<T*>(vs) + tid;
-    K[0] = k0;
-    V[0] = v0;
-    K[kSplitThreads] = k1;
-    V[kSplitThreads] = v1;
-    K[2 * kSplitThreads] = k2;
-    V[2 * kSplitThreads] = v2;
-  }
-};
+typedef TilePiece<128, 4> SplitPiece;   // three 16-byte pieces of K and of V per thread
 
 // tile0: the first 256-query tile of the list this launch covers.
 template <bool KTOK, bool SYM7, bool DEBUG, bool QB, bool LQ>

@@ -800,7 +800,7 @@ __device__ __forceinline__ void v_quant_e2m3(const VArgs& a, int tile, int bh, u
   for (int i = 0; i < 3; ++i) d[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
 }
 
-// LDS: the tile's codes (12 KB), 2 x 128 inverse scales, 8 x 2 x 128 floats.
+// LDS: the tile's codes (12 KB of E2M3 records, 8 KB of nibbles), 2 x 128 inverse scales, 8 x 2 x 128 floats.
 constexpr int kVQuantLdsBytes = kTile * 96 + 2 * kD * 4 + 8 * 2 * kD * 4;
 
 template <bool F16, bool VHAD>
@@ -854,40 +854,44 @@ __device__ __forceinline__ void v_quant_body(const VArgs& a, int tile, int bh, u
   if (a.center && a.mu_out && tile == 0 && rr == 0)
     *reinterpret_cast<float4*>(a.mu_out + bh * kD + 4 * cl) = mean4(a.sums + static_cast<size_t>(bh) * kD, a.N, cl);
   if (!a.local_amax) load_v_tile<F16, VHAD>(a, bh, tile, z);
-  if (a.e2m3) {
-    // group of 64 tokens gl = p/8, kappa = (p%8)*8 + rr, half h = (rr/4)%2; token kappa of a channel is
-    // field 8*((kappa%32)/8) + 2*(kappa%4) + kappa/32 of record ((gl*4 + ch/32)*2 + h)*32 + ch%32.
-    // The thread's codes for passes q and q+4 (q = p%4) are the adjacent fields 8q + 2*(rr%4) and
-    // +1: a 12-bit piece at bit 48q + 12*(rr%4); pieces are merged into LDS with atomic OR.
-    uint32_t* cw = reinterpret_cast<uint32_t*>(ctile);
-    for (int i = tid; i < kTile * 96 / 4; i += 256) cw[i] = 0u;
-    __syncthreads();
-    const int s4 = rr & 3, hh = (rr >> 2) & 1;
+  // E2M3 records of a rotated V (v_quant_e2m3 writes those of a V as it is)
+  if constexpr (VHAD) {
+    if (a.e2m3) {
+      // group of 64 tokens gl = p/8, kappa = (p%8)*8 + rr, half h = (rr/4)%2; token kappa of a channel is
+      // field 8*((kappa%32)/8) + 2*(kappa%4) + kappa/32 of record ((gl*4 + ch/32)*2 + h)*32 + ch%32.
+      // The thread's codes for passes q and q+4 (q = p%4) are the adjacent fields 8q + 2*(rr%4) and
+      // +1: a 12-bit piece at bit 48q + 12*(rr%4); pieces are merged into LDS with atomic OR.
+      uint32_t* cw = reinterpret_cast<uint32_t*>(ctile);
+      for (int i = tid; i < kTile * 96 / 4; i += 256) cw[i] = 0u;
+      __syncthreads();
+      const int s4 = rr & 3, hh = (rr >> 2) & 1;
 #pragma unroll
-    for (int gl = 0; gl < 2; ++gl) {
+      for (int gl = 0; gl < 2; ++gl) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int ch = 4 * cl + c;
-        const float inv = ginv[gl][ch];
-        const int rec = ((gl * 4 + (ch >> 5)) * 2 + hh) * 32 + (ch & 31);
+        for (int c = 0; c < 4; ++c) {
+          const int ch = 4 * cl + c;
+          const float inv = ginv[gl][ch];
+          const int rec = ((gl * 4 + (ch >> 5)) * 2 + hh) * 32 + (ch & 31);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t piece = e2m3_of(qcode(z[gl * 8 + q][c], inv)) | (e2m3_of(qcode(z[gl * 8 + q + 4][c], inv)) << 6);
-          const int b = 48 * q + 12 * s4;
-          const int w = rec * 6 + (b >> 5), sh = b & 31;
-          atomicOr(&cw[w], piece << sh);
-          if (sh > 20) atomicOr(&cw[w + 1], piece >> (32 - sh));
+          for (int q = 0; q < 4; ++q) {
+            const uint32_t piece =
+                e2m3_of(qcode(z[gl * 8 + q][c], inv)) | (e2m3_of(qcode(z[gl * 8 + q + 4][c], inv)) << 6);
+            const int b = 48 * q + 12 * s4;
+            const int w = rec * 6 + (b >> 5), sh = b & 31;
+            atomicOr(&cw[w], piece << sh);
+            if (sh > 20) atomicOr(&cw[w + 1], piece >> (32 - sh));
+          }
         }
       }
-    }
-    __syncthreads();
-    uint8_t* dst = a.codes + static_cast<size_t>(bh) * a.Npad * 96 + static_cast<size_t>(tile) * kTile * 96;
+      __syncthreads();
+      uint8_t* dst = a.codes + static_cast<size_t>(bh) * a.Npad * 96 + static_cast<size_t>(tile) * kTile * 96;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int o = (i * 256 + tid) * 16;
-      *reinterpret_cast<uint4*>(dst + o) = *reinterpret_cast<const uint4*>(&ctile[o]);
+      for (int i = 0; i < 3; ++i) {
+        const int o = (i * 256 + tid) * 16;
+        *reinterpret_cast<uint4*>(dst + o) = *reinterpret_cast<const uint4*>(&ctile[o]);
+      }
+      return;
     }
-    return;
   }
   // token kappa = (p%4)*8 + rr inside chunk p/4; nibble np = 8*(kappa/16) + 2*(kappa%4) + (kappa/8)%2,
   // half h = (kappa/4)%2; byte ((chunk*2 + h)*128 + ch)*8 + np/2.  Passes p and p+1 (p even)
