@@ -77,7 +77,8 @@ def test_fp16_fallback_parity(ora, wname, dtype, kv):
 
 # sequence lengths around whole numbers of 64- and 128-key blocks (the kernel
 # takes a block's scores during the previous block, so the first and the last
-# blocks take their own paths)
+# blocks take their own paths; one head, so these run on the key-split kernel:
+# test_gpu_tile_plan.py has the 4- and 8-wave kernels over several blocks)
 BOUNDARY_GRIDS = {64: (1, 8, 8), 128: (2, 8, 8), 129: (3, 43, 1), 192: (3, 8, 8), 256: (4, 8, 8),
                   257: (1, 1, 257), 384: (6, 8, 8), 385: (5, 7, 11)}
 

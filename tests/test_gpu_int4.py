@@ -124,7 +124,9 @@ def test_int4_codes_scores_and_output(ora, wname, case, fmt):
 # sequence lengths around whole numbers of 64- and 128-key blocks: one, two,
 # three and four blocks, each full and with a partial last block (the kernels
 # compute a block's scores during the previous block, so the first and last
-# blocks take their own paths)
+# blocks take their own paths).  One head: at kv_block 128 of the E2M3 container
+# these run on the key-split kernel, and test_gpu_tile_plan.py has the 4- and
+# 8-wave kernels over several blocks.
 BOUNDARY_GRIDS = {64: (1, 8, 8), 128: (2, 8, 8), 129: (3, 43, 1), 192: (3, 8, 8), 256: (4, 8, 8),
                   257: (1, 1, 257), 384: (6, 8, 8), 385: (5, 7, 11), 512: (8, 8, 8)}
 

@@ -33,6 +33,16 @@ PLANS = [
     (129, (1, 1, 257), (2, 1, 16, 128, 128, 0, 3, 0, 0)),      # 258: 256 plain, 2 in quarters (the last head)
     (257, (1, 8, 8), (1, 128, 64, 128, 128, 0, 3, 0, 0)),      # 256 plain, 1 in quarters, half a block of keys
     (130, (1, 15, 25), (3, 1, 128, 1 << 20, 128, 0, 4, 0, 0)), # 260, V scales per channel, Q smoothing alone
+    # five full blocks and six with a partial last one, where every one of the three
+    # tile buffers has been filled twice
+    (22, (5, 8, 16), (1, 128, 128, 256, 128, 0, 3, 0, 0)),     # 66 in halves, V groups of two blocks
+    (22, (5, 3, 47), (2, 128, 64, 256, 128, 1, 3, 0, 0)),      # 66 in halves, SYM7
+    (22, (5, 3, 47), (1, 128, 128, 128, 128, 0, 7, 0, 0)),     # 66 in halves, key bias
+    (22, (5, 3, 47), (1, 1, 1, 256, 128, 0, 3, 0, 0)),         # 66 in quarters, per-token
+    (22, (5, 3, 47), (1, 128, 32, 128, 64, 0, 7, 0, 0)),       # 66 in halves, 12 blocks of 64, key bias
+    (65, (5, 8, 16), (1, 128, 128, 256, 128, 0, 3, 0, 0)),     # 195 plain
+    (65, (5, 3, 47), (2, 128, 64, 256, 128, 1, 3, 0, 0)),      # 195 plain, SYM7
+    (65, (5, 3, 47), (1, 1, 1, 128, 64, 0, 3, 0, 0)),          # 195 plain, 12 blocks of 64, per-token
 ]
 
 
@@ -135,11 +145,14 @@ def test_fallback_tiles(ora, heads, grid, kv, fp16):
 
 
 @pytest.mark.parametrize("kv", [64, 128])
-@pytest.mark.parametrize("heads,grid", [(86, (5, 8, 16)), (129, (2, 15, 15)), (165, (2, 15, 15))])
+@pytest.mark.parametrize("heads,grid", [(86, (5, 8, 16)), (129, (2, 15, 15)), (165, (2, 15, 15)), (22, (5, 8, 16)),
+                                        (22, (5, 3, 47)), (65, (5, 8, 16)), (65, (5, 3, 47))])
 def test_fallback_tiles_of_several_blocks(ora, heads, grid, kv):
     """86 heads of 640 tokens: 430 tiles of 128 queries on 4 waves (kv_block 64),
     258 of 256 queries at kv_block 128; 129 and 165 heads of 450 tokens, two
-    256-query tiles each: a whole round and the rest in quarters or halves.
+    256-query tiles each: a whole round and the rest in quarters or halves; 22 and
+    65 heads of 640 and 705 tokens, three tiles each: 66 in halves, 195 on 8 waves,
+    the last block full and partial.
     (bfloat16 alone, since both types share every index: in binary16 the kernel's
     RoPE and the oracle's round some elements next to a tie to different
     neighbours, and one of K in these inputs, 11.43 +- 2^-7, moves O by 2.1e-3.)"""

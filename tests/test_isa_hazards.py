@@ -31,7 +31,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2607_02584_amd", "csrc")
 SOURCES = [os.path.join(CSRC, "ra_attn_e2m3.hip"), os.path.join(CSRC, "ra_attn_e2m3_debug.hip"),
-           os.path.join(CSRC, "ra_producer.hip")]
+           os.path.join(CSRC, "ra_producer.hip"), os.path.join(CSRC, "ra_fp16.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CONV = "v_cvt_scalef32_2xpk16_fp6_f32"
 
@@ -74,7 +74,7 @@ _ASM_CACHE = []
 
 
 def _asm():
-    """gfx950 assembly of the translation units (attention, debug attention, producers), compiled in parallel
+    """gfx950 assembly of the translation units (attention, debug attention, producers, fallback), compiled in parallel
     once per test session."""
     if not _ASM_CACHE:
         _ASM_CACHE.append(_compile())
@@ -140,5 +140,6 @@ def test_no_kernel_uses_scratch():
             continue                      # debug dump instantiation
         if z > 0:
             bad.append((n, z))
-    assert any("k_pass" in n for n in names) and any("k_attn_e2m3" in n for n in names)
+    for kernel in ("k_pass", "k_attn_e2m3", "k_attn_e2m3_split", "k_attn16", "k_attn16_split", "k_rope16"):
+        assert any(kernel in n for n in names), kernel
     assert not bad, f"kernels with a private segment: {bad}"
