@@ -30,8 +30,9 @@ struct TilePlan {
 // fill the LDS), all run on 4 waves.  Measured, the attention alone, divided
 // tiles / all on 4 waves: 64 tokens, 640 heads 22.7 / 14.2 us; 384 tokens, 129
 // heads 28.2 / 17.7; 1560 tokens, 37 heads 80 / 55; 4224 tokens, 31 heads 323 /
-// 270.  Where both take the same rounds the two are alike below 1000 tokens and
-// the 8 waves faster above (4224 tokens, 48 heads 457 / 471 us).
+// 270.  Where both take the same rounds the 8 waves are the faster from about 1000
+// tokens on (1024 tokens, 65 heads 56.6 / 58.8 us); below, 4 waves take up to 13 %
+// less (256 tokens, 340 heads 26.8 / 23.3), which this rule leaves.
 inline TilePlan plan_fallback(int npad, int bh, int kv_block, int units) {
   const int total = (npad + 255) / 256 * bh, total128 = npad / 128 * bh;
   TilePlan p{0, 0, 0, 0};
