@@ -289,7 +289,7 @@ __device__ __forceinline__ void finish_rows(const Fp16Args& a, const v16f (&of)[
 // compute unit with one copy of the tiles: at kv_block 128 the tiles fill the
 // LDS, and 4 waves were alone with it (32760 tokens 7.40 -> 5.88 ms); at
 // kv_block 64 the unit's tile traffic halves (6.17 -> 5.95 ms; the kernel runs at
-// the power limit there, 2.05 GHz of 2.4).  4 (128 queries) are for a last round that
+// the power limit there, 1.93-2.05 GHz of 2.4).  4 (128 queries) are for a last round that
 // would leave units idle, and for heads that 256-query tiles fit badly.  The launch
 // covers a list of tiles of 32 NW queries, per_head of them a head, from tile u0 on.
 template <bool F16, int kKV, int NW>
